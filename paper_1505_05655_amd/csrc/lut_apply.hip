@@ -14,6 +14,21 @@
 
 namespace rc {
 
+typedef void (*ApplyKernel)(ApplyParams);
+
+// row[policy * kModes + mode], mode = rc_path value (raw LDS, L2, packed
+// LDS, dense LDS), policy = the plan's image cache policy (0..kPolicies-1)
+constexpr int kModes = 4;
+constexpr int kRow = kPolicies * kModes;
+
+// The kernels of one (pixels per lane, lines per register set). This file is
+// compiled once per pair with RC_APPLY_VEC and RC_APPLY_UNROLL defined, which
+// gives that pair's kernels, and once without, which gives the host side.
+template <int VEC, int UNROLL>
+void fill_row(ApplyKernel* row);
+
+#ifdef RC_APPLY_VEC
+
 // The dense mode runs at most 512 threads (its 160 KiB tile allows one
 // workgroup per CU, two waves per SIMD): the tighter bound leaves it the
 // registers to keep every pixel's LDS reads of a register set in flight.
@@ -62,6 +77,39 @@ __global__ __launch_bounds__(MODE == kDense ? kDenseMaxThreads : 1024) void k_ap
                                        p.dense != 0, p.pre_planes, p.pre_heads, ci, ck, p.threads);
 }
 
+template <int VEC, int UNROLL, int NT>
+void fill_policy(ApplyKernel* row) {
+    row[NT * kModes + 0] = k_apply<VEC, UNROLL, NT, kRaw>;
+    row[NT * kModes + 1] = k_apply<VEC, UNROLL, NT, kGlobal>;
+    row[NT * kModes + 2] = k_apply<VEC, UNROLL, NT, kPacked>;
+    row[NT * kModes + 3] = k_apply<VEC, UNROLL, NT, kDense>;
+}
+
+template <>
+void fill_row<RC_APPLY_VEC, RC_APPLY_UNROLL>(ApplyKernel* row) {
+    fill_policy<RC_APPLY_VEC, RC_APPLY_UNROLL, 0>(row);
+    fill_policy<RC_APPLY_VEC, RC_APPLY_UNROLL, 1>(row);
+    fill_policy<RC_APPLY_VEC, RC_APPLY_UNROLL, 2>(row);
+    fill_policy<RC_APPLY_VEC, RC_APPLY_UNROLL, 3>(row);
+    fill_policy<RC_APPLY_VEC, RC_APPLY_UNROLL, 4>(row);
+    fill_policy<RC_APPLY_VEC, RC_APPLY_UNROLL, 5>(row);
+    static_assert(kPolicies == 6, "one fill_policy per cache policy");
+}
+
+#else  // the host side and the encoder
+
+// Defined by the RC_APPLY_VEC / RC_APPLY_UNROLL compilations.
+template <> void fill_row<1, 4>(ApplyKernel* row);
+template <> void fill_row<1, 8>(ApplyKernel* row);
+template <> void fill_row<1, 16>(ApplyKernel* row);
+template <> void fill_row<2, 4>(ApplyKernel* row);
+template <> void fill_row<2, 8>(ApplyKernel* row);
+template <> void fill_row<2, 16>(ApplyKernel* row);
+template <> void fill_row<4, 4>(ApplyKernel* row);
+template <> void fill_row<4, 8>(ApplyKernel* row);
+template <> void fill_row<4, 16>(ApplyKernel* row);
+template <> void fill_row<8, 4>(ApplyKernel* row);
+
 // One thread per (row, 64-level block). Consecutive threads take the same
 // block of consecutive rows: their output words are consecutive (output
 // [band][block][detector]), and a wave's blocks are mostly of one kind
@@ -85,34 +133,7 @@ __global__ __launch_bounds__(256) void k_dense_encode(const uint16_t* __restrict
                            planes + o, heads + o);
 }
 
-typedef void (*ApplyKernel)(ApplyParams);
-
 namespace {
-
-// row[policy * kModes + mode], mode = rc_path value (raw LDS, L2, packed
-// LDS, dense LDS), policy = the plan's image cache policy (0..kPolicies-1)
-constexpr int kModes = 4;
-
-template <int VEC, int UNROLL, int NT>
-void fill_policy(ApplyKernel* row) {
-    row[NT * kModes + 0] = k_apply<VEC, UNROLL, NT, kRaw>;
-    row[NT * kModes + 1] = k_apply<VEC, UNROLL, NT, kGlobal>;
-    row[NT * kModes + 2] = k_apply<VEC, UNROLL, NT, kPacked>;
-    row[NT * kModes + 3] = k_apply<VEC, UNROLL, NT, kDense>;
-}
-
-template <int VEC, int UNROLL>
-void fill_row(ApplyKernel* row) {
-    fill_policy<VEC, UNROLL, 0>(row);
-    fill_policy<VEC, UNROLL, 1>(row);
-    fill_policy<VEC, UNROLL, 2>(row);
-    fill_policy<VEC, UNROLL, 3>(row);
-    fill_policy<VEC, UNROLL, 4>(row);
-    fill_policy<VEC, UNROLL, 5>(row);
-    static_assert(kPolicies == 6, "one fill_policy per cache policy");
-}
-
-constexpr int kRow = kPolicies * kModes;
 
 // table[vec index][unroll index][policy * kModes + mode]
 struct Table {
@@ -198,5 +219,7 @@ hipError_t launch_apply(const ApplyParams& p, const rc_plan& plan, size_t lds_by
                        plan.path == RC_PATH_L2 ? 0 : lds_bytes, stream, p);
     return hipGetLastError();
 }
+
+#endif  // RC_APPLY_VEC
 
 }  // namespace rc
