@@ -89,6 +89,24 @@ __device__ __forceinline__ typename Px<VEC>::T map_px(typename Px<VEC>::T w, F f
     }
 }
 
+// As map_px, with a second set of VEC 16-bit values: f(k, a_k, b_k).
+template <int VEC, typename F>
+__device__ __forceinline__ typename Px<VEC>::T map_px2(typename Px<VEC>::T a,
+                                                       typename Px<VEC>::T b, F f) {
+    if constexpr (VEC == 1) {
+        return (unsigned short)f(0, (uint32_t)a, (uint32_t)b);
+    } else if constexpr (VEC == 2) {
+        return f(0, a & 0xffffu, b & 0xffffu) | (f(1, a >> 16, b >> 16) << 16);
+    } else {
+        typename Px<VEC>::T r;
+#pragma unroll
+        for (int i = 0; i < VEC / 2; ++i)
+            r[i] = f(2 * i, a[i] & 0xffffu, b[i] & 0xffffu) |
+                   (f(2 * i + 1, a[i] >> 16, b[i] >> 16) << 16);
+        return r;
+    }
+}
+
 // Raw buffer resource over `bytes` bytes from `base` (gfx9-family word 3:
 // untyped 32-bit data). Buffer loads past `bytes` return 0 and stores past
 // it are dropped, so a tile's last partial pass needs no per-line guard.
@@ -171,12 +189,12 @@ template <int NT> struct Buf<8, NT> {
 // latency overlaps its own gather work (no register copies between the sets,
 // which would force a wait on the prefetched loads). The prefetch past the
 // last pass falls outside the buffer range (loads of 0); offsets stay below
-// 2^31 because tiles are sized with two passes of slack.
-template <int VEC, int UNROLL, int NT, typename G>
-__device__ __forceinline__ void stream_lines(__amdgpu_buffer_rsrc_t rin,
-                                             __amdgpu_buffer_rsrc_t rout, uint32_t vo,
-                                             uint32_t line_stride, int passes, G gather,
-                                             uint32_t pass_adv = 0) {
+// 2^31 because tiles are sized with two passes of slack. emit(set, so)
+// corrects and stores the UNROLL lines of a register set at line offset so.
+template <int VEC, int UNROLL, int NT, typename E>
+__device__ __forceinline__ void stream_sets(__amdgpu_buffer_rsrc_t rin, uint32_t vo,
+                                            uint32_t line_stride, int passes, uint32_t pass_adv,
+                                            E emit) {
     typedef typename Px<VEC>::T T;
     const uint32_t pass_bytes = pass_adv ? pass_adv : UNROLL * line_stride;
     T a[UNROLL], b[UNROLL];
@@ -188,19 +206,30 @@ __device__ __forceinline__ void stream_lines(__amdgpu_buffer_rsrc_t rin,
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u)
             b[u] = Buf<VEC, NT>::ld(rin, vo, so + pass_bytes + u * line_stride);
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u)
-            Buf<VEC, NT>::st(rout, vo, so + u * line_stride, map_px<VEC>(a[u], gather));
+        emit(a, so);
         if (k + 1 >= passes) break;
         so += pass_bytes;
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u)
             a[u] = Buf<VEC, NT>::ld(rin, vo, so + pass_bytes + u * line_stride);
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u)
-            Buf<VEC, NT>::st(rout, vo, so + u * line_stride, map_px<VEC>(b[u], gather));
+        emit(b, so);
         so += pass_bytes;
     }
+}
+
+// stream_sets with one call gather(k, dn) per pixel k of the lane.
+template <int VEC, int UNROLL, int NT, typename G>
+__device__ __forceinline__ void stream_lines(__amdgpu_buffer_rsrc_t rin,
+                                             __amdgpu_buffer_rsrc_t rout, uint32_t vo,
+                                             uint32_t line_stride, int passes, G gather,
+                                             uint32_t pass_adv = 0) {
+    typedef typename Px<VEC>::T T;
+    stream_sets<VEC, UNROLL, NT>(
+        rin, vo, line_stride, passes, pass_adv, [&](const T (&w)[UNROLL], uint32_t so) {
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u)
+                Buf<VEC, NT>::st(rout, vo, so + u * line_stride, map_px<VEC>(w[u], gather));
+        });
 }
 
 // ---- the three LUT access modes -------------------------------------------------------
@@ -308,17 +337,25 @@ __device__ __forceinline__ int bcnt_acc(uint32_t x, int acc) {
 
 // p8 = 8p, h2 = NB*W*8 + 2p (the lane's position p in the plane and header
 // arrays, in bytes from the start of LDS).
-__device__ __forceinline__ uint32_t g_dense(uint32_t dnv, uint32_t top, int logW, uint32_t p8,
-                                            uint32_t h2) {
+// hmin: lowered to the header read.
+__device__ __forceinline__ uint32_t g_dense_min(uint32_t dnv, uint32_t top, int logW, uint32_t p8,
+                                                uint32_t h2, int& hmin) {
     const uint32_t v = dnv < top ? dnv : top;
     const uint32_t blk = v >> 6;
     const uint64_t z = *(lds_u64*)(uintptr_t)((blk << (logW + 3)) + p8);
     const int h = *(lds_i16*)(uintptr_t)((blk << (logW + 1)) + h2);
+    hmin = min(hmin, h);
     const uint64_t sh = z << (v & 63u);
     int u = (int)(v << ((uint32_t)z & 1u)) + h;
     u = bcnt_acc((uint32_t)(sh >> 32), u);
     u = bcnt_acc((uint32_t)sh, u);
     return clamp0(u, (int)top);
+}
+
+__device__ __forceinline__ uint32_t g_dense(uint32_t dnv, uint32_t top, int logW, uint32_t p8,
+                                            uint32_t h2) {
+    int unused = 0;
+    return g_dense_min(dnv, top, logW, p8, h2, unused);
 }
 
 // As g_dense, for a strip with blocks the dense form cannot hold: a level of
@@ -448,15 +485,34 @@ __device__ __forceinline__ void dense_encode_row_block(const uint16_t* row, int 
     *head = hd;
 }
 
-// Workgroup-wide OR of `flag` for a dense strip, without static LDS: a
-// wave with the flag set writes kDenseBad (a header no encodable block has)
-// over the first header; the tile then does not decode the strip. Call
-// after every thread has staged; every thread returns the same value.
-__device__ __forceinline__ int dense_any(int flag, int16_t* heads) {
+// Blocks of a dense strip the form cannot hold, summed over the workgroup
+// from each thread's count, without static LDS (a strip may fill the LDS): if
+// any wave has one, the strip's first plane and header words are lent to a
+// flag and the sum, and put back. Call after every thread has staged; every
+// thread returns the same value.
+__device__ __forceinline__ uint32_t dense_bad_blocks(int count, uint64_t* planes, int16_t* heads) {
     __syncthreads();
-    if (__any(flag) && (threadIdx.x & 63) == 0) heads[0] = kDenseBad;
+    const int16_t h0 = heads[0];
+    const uint64_t z0 = planes[0];
     __syncthreads();
-    return (int)(heads[0] == kDenseBad);
+    if (threadIdx.x == 0) {
+        heads[0] = 0;
+        planes[0] = 0;
+    }
+    __syncthreads();
+    if (__any(count)) {
+        if ((threadIdx.x & 63) == 0) heads[0] = 1;
+        if (count) atomicAdd((unsigned int*)planes, (unsigned int)count);
+    }
+    __syncthreads();
+    const uint32_t n = heads[0] ? *(const unsigned int*)planes : 0u;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        heads[0] = h0;
+        planes[0] = z0;
+    }
+    __syncthreads();
+    return n;
 }
 
 enum TileMode { kRaw = 0, kGlobal = 1, kPacked = 2, kDense = 3 };
@@ -607,7 +663,7 @@ __device__ __forceinline__ void apply_tile(const uint16_t* dn, const uint16_t* _
                 const size_t g = row0 + (size_t)blk * (size_t)D + (size_t)jj;
                 const int16_t hd = pre_heads[g];
                 const int p = ((jj & (VEC - 1)) << logq) + (jj >> LOGVEC);
-                bad |= (int)(hd == kDenseBad);
+                bad += (int)(hd == kDenseBad);
                 planes[(blk << logW) + p] = pre_planes[g];
                 heads[(blk << logW) + p] = hd;
             }
@@ -643,29 +699,92 @@ __device__ __forceinline__ void apply_tile(const uint16_t* dn, const uint16_t* _
             }
             uint64_t pl = 0;
             int16_t hd = kDenseBad;
-            if (!dense_encode(e, cnt, top, blk, &pl, &hd)) bad = 1;
+            if (!dense_encode(e, cnt, top, blk, &pl, &hd)) ++bad;
             planes[u] = pl;
             heads[u] = hd;
         }
-        bad = dense_any(bad, heads);
-        if (streams) {
-            if (!bad) {
+        const uint32_t nbad = dense_bad_blocks(bad, planes, heads);
+        if (nbad == 0) {
+            if (streams)
                 stream_lines<VEC, UNROLL, NT>(
                     rin, rout, vo, line_stride, passes, [&](int k, uint32_t d) {
                         const uint32_t p = (uint32_t)((k << logq) + lane);
                         return g_dense(d, top, logW, p * 8u, hb + p * 2u);
                     }, pass_adv);
+        } else {
+            // Some blocks of the strip are not held in dense form (one or two
+            // per million of a calibration LUT, so every second or third
+            // large 12-bit scene has a tile with one, which then must not be
+            // the last to finish). Their levels read the global LUT row. The
+            // threads that only staged stream too: thread group g of ng takes
+            // every ng-th of the tile's passes, while the offsets of its
+            // prefetch stay within the 32-bit range.
+            const int per = nst ? nst : nt;
+            const int ng0 = nt / per;
+            const bool fits = ((uint64_t)passes + 3u * (uint64_t)ng0 + (uint64_t)ck) *
+                                  (uint64_t)pass_adv < ((uint64_t)1 << 31);
+            const int ng = __builtin_amdgcn_readfirstlane(fits ? ng0 : 1);
+            // Whole waves: per is a multiple of 64.
+            const int grp = __builtin_amdgcn_readfirstlane(tid / per);
+            const int gtid = tid - grp * per;
+            const int grow = gtid / q;
+            const int glane = gtid - grow * q;
+            const int gj = glane * VEC;
+            const uint32_t gvo = (uint32_t)(((size_t)grow * (size_t)D + (size_t)gj) * 2) +
+                                 (uint32_t)ci * pass_bytes + (uint32_t)grp * pass_adv;
+            const uint32_t gadv = (uint32_t)ng * pass_adv;
+            const int gpasses = grp < passes ? (passes - grp + ng - 1) / ng : 0;
+            const uint16_t* lrow = strip_lut + (size_t)gj * Lz;
+            if (grp >= ng || grow >= rpp || gj >= weff || gpasses == 0) {
+                // nothing to stream
+            } else if (nbad <= (uint32_t)NB) {
+                // Few: decode every pixel and keep the smallest header the
+                // lane read in each line; a lane that met such a block then
+                // takes those pixels from the LUT row. One branch per
+                // register set, so that the LDS reads of a set stay in flight
+                // together; nbad <= NB bounds how often it is taken (about
+                // one pixel in weff).
+                typedef typename Px<VEC>::T T;
+                stream_sets<VEC, UNROLL, NT>(
+                    rin, gvo, line_stride, gpasses, gadv,
+                    [&](const T (&w)[UNROLL], uint32_t so) {
+                        int hmin[UNROLL], hset = 0;
+                        T r[UNROLL];
+#pragma unroll
+                        for (int u = 0; u < UNROLL; ++u) {
+                            hmin[u] = 0;
+                            r[u] = map_px<VEC>(w[u], [&](int k, uint32_t d) {
+                                const uint32_t p = (uint32_t)((k << logq) + glane);
+                                return g_dense_min(d, top, logW, p * 8u, hb + p * 2u, hmin[u]);
+                            });
+                            hset = min(hset, hmin[u]);
+                        }
+                        if (hset == (int)kDenseBad) {
+#pragma unroll
+                            for (int u = 0; u < UNROLL; ++u)
+                                if (hmin[u] == (int)kDenseBad)
+                                    r[u] = map_px2<VEC>(w[u], r[u], [&](int k, uint32_t d,
+                                                                        uint32_t e) {
+                                        const uint32_t v = d < top ? d : top;
+                                        const uint32_t p = (uint32_t)((k << logq) + glane);
+                                        const int h = *(lds_i16*)(uintptr_t)(
+                                            ((v >> 6) << (logW + 1)) + hb + p * 2u);
+                                        const uint32_t g = lrow[(size_t)k * Lz + v];
+                                        return h == (int)kDenseBad ? g : e;
+                                    });
+                        }
+#pragma unroll
+                        for (int u = 0; u < UNROLL; ++u)
+                            Buf<VEC, NT>::st(rout, gvo, so + u * line_stride, r[u]);
+                    });
             } else {
-                // Some blocks of the strip (or, with the flag's word, block 0
-                // of its first position) are not held in dense form: their
-                // levels read the global LUT row, every other level decodes.
-                const uint16_t* lrow = strip_lut + (size_t)j * Lz;
+                // Many: check every header before decoding.
                 stream_lines<VEC, UNROLL, NT>(
-                    rin, rout, vo, line_stride, passes, [&](int k, uint32_t d) {
-                        const uint32_t p = (uint32_t)((k << logq) + lane);
+                    rin, rout, gvo, line_stride, gpasses, [&](int k, uint32_t d) {
+                        const uint32_t p = (uint32_t)((k << logq) + glane);
                         return g_dense_checked(d, top, logW, p * 8u, hb + p * 2u,
                                                lrow + (size_t)k * Lz);
-                    }, pass_adv);
+                    }, gadv);
             }
         }
         __syncthreads();  // the tile may be restaged next
