@@ -206,18 +206,92 @@ bool balanced_tiling(int64_t lines, int32_t detectors, int32_t bands, int vec, i
     return true;
 }
 
-// Default launch shape (no tuning), from measurements on MI355X. Two tilings:
-//  - power-of-two strips of W detectors in an 80 KiB LDS tile (W = 256 for
-//    L <= 2048: 512-byte line segments), one line chunk when that already
-//    gives most CUs a tile (pow2_plan);
-//  - when the CU share of the detectors (bands x detectors / CUs) is wider
-//    than that W (long LUT rows: W = 64 at L = 4096), one tile per CU: each
-//    band cut into strips of equal width so that the tile count matches the
-//    CU count, the LUT strip in a 160 KiB tile staged once, 256 threads
-//    (one wave per SIMD, 2 pixels x 8 lines per lane and register set, no
-//    idle lanes), which keeps the fewest lines in flight per CU for the bytes
-//    it moves: more threads per CU made the L2 re-fetch the partial cache
-//    lines that neighbouring strips share (measured 1.7x the reads with 1024).
+// The power-of-two strip W (raw or packed) and line chunk count k of least
+// estimated time, 256 threads with 16 bytes x 4 lines per lane and register
+// set (half or twice the bytes in flight per CU were slower by 20 % and 10 %
+// on every large scene). The estimate, in us, of a launch of B x ceil(D / W)
+// x k tiles:
+//  - staging a tile: W x L entries at 0.22 ns (packed) or 0.115 ns (raw);
+//  - streaming: the image at 6 TB/s (and 21 GB/s per tile) times W / (W + 5 +
+//    50 min(1, lines per tile / 20000)): neighbouring strips share the memory
+//    sectors at their ends, the more often twice the further their tiles have
+//    drifted apart;
+//  - one round of tiles (at most one per CU) stages, then streams; more tiles
+//    overlap the two, but their streams, far apart in the image, run at a
+//    third of the rate, which only a scene with fewer lines than levels makes
+//    up for.
+// Fitted to 32 scenes of 1-4 bands, 512-50000 lines, 512-12000 detectors and
+// 1024 or 4096 levels, timed with every W in {8 .. 512} and about 8 chunk
+// counts each: the plan chosen takes 1.03 times the best one's time on
+// average, 1.13 at worst, and was at least as fast as the former default (W =
+// 256 or 64, about two rounds of 512-thread tiles but few line chunks) on all:
+// 1 x 30000 x 2000 at 4096 levels 69 against 163 us, 4 x 3000 x 1000 at 1024
+// 14 against 103, 1 x 512 x 512 8 against 34, 3 x 5400 x 4096 68 against 111,
+// 4 x 12000 x 12000 466 against 460 (a tuned plan). False if nothing fits.
+bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
+                const DeviceInfo& di, rc_plan* plan) {
+    const int64_t cus = std::max(1, di.cus);
+    const size_t budget = std::min(di.lds ? di.lds : (size_t)65536,
+                                   di.lds_per_cu ? di.lds_per_cu : (size_t)65536);
+    rc_plan p;
+    std::memset(&p, 0, sizeof(p));
+    p.threads = 256;
+    p.xcd_remap = 1;
+    double best = 0.0;
+    bool found = false;
+    const double image = 4.0 * (double)bands * (double)lines * (double)detectors;
+    for (int W = 8; W <= 512; W <<= 1) {
+        if (W > 8 && W / 2 >= detectors) break;
+        const int vec = std::min(std::min(vmax, 8), W);
+        const int unroll = vec == 8 ? 4 : 8;
+        const int64_t cap = max_chunk_lines(detectors, p.threads, unroll);
+        if (cap < 1) return false;
+        const int64_t kmin = std::max<int64_t>(1, (lines + cap - 1) / cap);
+        const int64_t strips = ((int64_t)detectors + W - 1) / W;
+        const int64_t base = strips * bands;
+        const double w = std::min(W, detectors);
+        for (int path : {RC_PATH_LDS, RC_PATH_PACKED}) {
+            if (path == RC_PATH_PACKED && levels < 512) continue;
+            const size_t lds = plan_lds_bytes(path, W, levels);
+            if (lds > budget) continue;
+            const double stage = w * levels * (path == RC_PATH_LDS ? 1.15e-4 : 2.2e-4);
+            const int64_t kmax = std::max(kmin, std::min<int64_t>(cus / base, lines));
+            for (int64_t k = kmin; k <= kmax; ++k) {
+                const double per_tile = (double)lines / (double)k;
+                // Lines a pass takes, and the share of the last one's that exist.
+                const double pass = (double)std::max(1, p.threads / std::max(1, W / vec)) * unroll;
+                const double waste = std::min(1.5, std::ceil(per_tile / pass) * pass / per_tile);
+                const double eff = w / (w + 5.0 + 50.0 * std::min(1.0, per_tile / 20000.0));
+                const int64_t tiles = base * k;
+                const bool one_round = tiles <= cus;
+                const double rate = one_round ? std::min(6e6 * eff, 21e3 * (double)tiles)
+                                              : 2e6 * eff;  // bytes per us
+                const double stream = image * waste / rate;
+                const int conc = (int)std::max<size_t>(1, std::min<size_t>(8, budget / lds));
+                const double stages = stage * (double)((tiles + cus - 1) / cus);
+                const double t = one_round || conc == 1 ? stages + stream
+                                                        : std::max(stages, stream) + stage;
+                if (found && t >= best) continue;
+                found = true;
+                best = t;
+                p.path = path;
+                p.strip = W;
+                p.vec = vec;
+                p.unroll = unroll;
+                p.chunk_lines = (int32_t)std::min<int64_t>((lines + k - 1) / k, INT32_MAX);
+            }
+        }
+    }
+    // Non-temporal stores gain 2-8 % where every segment is whole 64-byte
+    // sectors and lose up to 25 % where neighbouring tiles complete them.
+    p.nontemporal = detectors % 32 == 0 && p.strip >= 32 ? 2 : 0;
+    if (found) *plan = p;
+    return found;
+}
+
+// Default launch shape (no tuning): dense strips of up to 256 detectors for
+// long LUT rows with many lines per tile, else strip_plan, else pow2_plan (the
+// L2 path, for LUT rows too long for LDS strips).
 void default_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
                   const DeviceInfo& di, rc_plan* plan) {
     rc_plan legacy;
@@ -254,38 +328,13 @@ void default_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t level
         *plan = p;
         return;
     }
-    const double share = (double)bands * (double)detectors / (double)cus;
-    // One tile per CU stages a whole strip with few waves: worth it only when
-    // the strip then streams many lines (at least 4 L).
-    if (legacy.path == RC_PATH_L2 || share <= (double)legacy.strip ||
-        lines < 4 * (int64_t)levels) {
+    if (legacy.path == RC_PATH_L2 || !strip_plan(lines, detectors, bands, levels, vmax, di, plan))
         *plan = legacy;
-        return;
-    }
-    const int path_lds = levels >= 512 ? RC_PATH_PACKED : RC_PATH_LDS;
-    const size_t budget = std::min(di.lds ? di.lds : (size_t)65536,
-                                   di.lds_per_cu ? di.lds_per_cu : (size_t)65536);
-    const int wmax = widest_strip(path_lds, levels, budget);
-    rc_plan p;
-    std::memset(&p, 0, sizeof(p));
-    p.path = path_lds;
-    p.vec = std::min(vmax, 2);
-    p.threads = 256;
-    p.unroll = 8;
-    p.xcd_remap = 1;
-    p.nontemporal = 0;
-    p.lane_map = 1;
-    if (wmax < 16 || !balanced_tiling(lines, detectors, bands, p.vec, wmax, cus, p.threads,
-                                      p.unroll, &p.strips, &p.strip, &p.chunk_lines)) {
-        *plan = legacy;
-        return;
-    }
-    *plan = p;
 }
 
 rc_status check_plan(const rc_plan& plan, int64_t lines, int32_t detectors, int32_t bands,
                      int32_t levels, int vmax, const DeviceInfo& di, ApplyParams* p,
-                     size_t* lds_bytes) {
+                     size_t* lds_bytes, bool wide) {
     if (plan.path != RC_PATH_LDS && plan.path != RC_PATH_L2 && plan.path != RC_PATH_PACKED &&
         plan.path != RC_PATH_DENSE)
         return RC_EINVAL;
@@ -293,7 +342,7 @@ rc_status check_plan(const rc_plan& plan, int64_t lines, int32_t detectors, int3
     if (plan.path == RC_PATH_DENSE && plan.threads > kDenseMaxThreads) return RC_EINVAL;
     if (!is_pow2(plan.strip) || plan.strip > 1024) return RC_EINVAL;
     if (plan.vec != 1 && plan.vec != 2 && plan.vec != 4 && plan.vec != 8) return RC_EINVAL;
-    if (plan.vec > vmax || plan.strip < plan.vec) return RC_EINVAL;
+    if ((plan.vec > vmax && !wide) || plan.strip < plan.vec) return RC_EINVAL;
     if (plan.threads != 256 && plan.threads != 512 && plan.threads != 1024) return RC_EINVAL;
     if (plan.unroll != 4 && plan.unroll != 8 && plan.unroll != 16) return RC_EINVAL;
     if (plan.vec == 8 && plan.unroll != 4) return RC_EINVAL;  // would spill registers
@@ -308,12 +357,17 @@ rc_status check_plan(const rc_plan& plan, int64_t lines, int32_t detectors, int3
     if (plan.strips < 0) return RC_EINVAL;
     int64_t strips = (detectors + (int64_t)plan.strip - 1) / plan.strip;
     if (plan.strips > 0) {
-        // vec divides detectors (vec <= vmax); strips of whole vec units, the
-        // widest ceil(units / strips) units, at most W detectors.
-        const int64_t units = detectors / plan.vec;
+        // Strips of whole vec units (vec divides detectors, or `wide`: the
+        // last unit may be partial), the widest ceil(units / strips) units,
+        // at most W detectors.
+        const int64_t units = (detectors + plan.vec - 1) / plan.vec;
         if (plan.strips > units) return RC_EINVAL;
         if (plan.vec * ((units + plan.strips - 1) / plan.strips) > plan.strip) return RC_EINVAL;
         strips = plan.strips;
+        // The last strip has at least vec detectors.
+        if (wide && (detectors < plan.vec || (strips > 1 && units / strips < 2))) return RC_EINVAL;
+    } else if (wide && detectors - (strips - 1) * plan.strip < plan.vec) {
+        return RC_EINVAL;
     }
     const int64_t chunks = (lines + plan.chunk_lines - 1) / plan.chunk_lines;
     int64_t tiles = 0;
@@ -434,12 +488,31 @@ void ws_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, in
     *plan = p;
 }
 
+bool widen_plan(const uint16_t* dn, const uint16_t* out, int32_t detectors, rc_plan* plan) {
+    rc_plan p = *plan;
+    if (p.path == RC_PATH_L2 || p.vec == 8 || dn == out || p.strip < 8 || detectors < 8)
+        return false;
+    const int64_t pow2 = ((int64_t)detectors + p.strip - 1) / p.strip;
+    if (p.strips > 0 || detectors - (pow2 - 1) * p.strip < 8) {
+        const int64_t units = ((int64_t)detectors + 7) / 8;
+        const int64_t fit = (units + p.strip / 8 - 1) / (p.strip / 8);  // at most p.strip wide
+        const int64_t strips = std::max<int64_t>(fit, p.strips > 0 ? p.strips : pow2);
+        if (strips > 1 && units / strips < 2) return false;
+        p.strips = (int32_t)strips;
+        p.lane_map = 1;
+    }
+    p.vec = 8;
+    p.unroll = 4;
+    *plan = p;
+    return true;
+}
+
 namespace {
 
 rc_status run_correct(const uint16_t* dn, const uint16_t* lut, int64_t lines, int32_t detectors,
                       int32_t bands, int32_t levels, uint16_t* out, const rc_plan* forced,
                       hipStream_t stream, void* ws = nullptr, size_t ws_bytes = 0,
-                      bool pre_encoded = false) {
+                      bool pre_encoded = false, bool may_widen = false) {
     bool empty = false;
     rc_status st = validate_correct(dn, lut, lines, detectors, bands, levels, out, &empty);
     if (st != RC_OK || empty) return st;
@@ -474,7 +547,15 @@ rc_status run_correct(const uint16_t* dn, const uint16_t* lut, int64_t lines, in
     if (use_ws && plan.path != RC_PATH_DENSE) return RC_EINVAL;
     ApplyParams p{};
     size_t lds_bytes = 0;
-    st = check_plan(plan, lines, detectors, bands, levels, vmax, *di, &p, &lds_bytes);
+    // A plan the caller asked for runs as it is; one the library chose takes 8
+    // pixels per lane where that fits.
+    rc_plan wide = plan;
+    if ((!forced || may_widen) && vmax < 8 && widen_plan(dn, out, detectors, &wide) &&
+        check_plan(wide, lines, detectors, bands, levels, vmax, *di, &p, &lds_bytes, true) ==
+            RC_OK)
+        plan = wide;
+    else
+        st = check_plan(plan, lines, detectors, bands, levels, vmax, *di, &p, &lds_bytes);
     if (st != RC_OK) return st;
     p.dn = dn;
     p.lut = lut;
@@ -482,7 +563,8 @@ rc_status run_correct(const uint16_t* dn, const uint16_t* lut, int64_t lines, in
     p.lut_vec = (levels % 8 == 0 && ((uintptr_t)lut & 15u) == 0) ? 1 : 0;
     if (use_ws) {
         if (!pre_encoded) {
-            hipError_t e = launch_dense_encode(lut, bands, detectors, levels, planes, heads, stream);
+            hipError_t e = launch_dense_encode(lut, bands, detectors, levels, planes, heads,
+                                               di->xcds, stream);
             if (e != hipSuccess) return hip_fail(e);
         }
         p.pre_planes = planes;
@@ -505,6 +587,14 @@ rc_status run_correct(const uint16_t* dn, const uint16_t* lut, int64_t lines, in
 }
 
 }  // namespace
+
+rc_status correct_chosen(const uint16_t* dn, const uint16_t* lut, int64_t lines,
+                         int32_t detectors, int32_t bands, int32_t levels, uint16_t* out,
+                         const rc_plan& plan, hipStream_t stream) {
+    return run_correct(dn, lut, lines, detectors, bands, levels, out, &plan, stream, nullptr, 0,
+                       false, true);
+}
+
 }  // namespace rc
 
 using namespace rc;
@@ -592,14 +682,15 @@ rc_status rc_lut_build_ws(const double* coeffs, int32_t bands, int32_t detectors
     if (overlaps(coeffs, (size_t)cbytes, lut, (size_t)lbytes) ||
         overlaps(ws, need, coeffs, (size_t)cbytes) || overlaps(ws, need, lut, (size_t)lbytes))
         return RC_EINVAL;
-    int dev = 0;
-    if (!current_device(&dev)) return RC_EHIP;
+    const DeviceInfo* di = current_device();
+    if (!di) return RC_EHIP;
     // The split run_correct uses: planes from byte 0, headers from the next
     // 256-byte boundary after them.
     const size_t n = (size_t)rows * (size_t)((levels + 63) / 64);
     uint64_t* planes = (uint64_t*)ws;
     int16_t* heads = (int16_t*)((char*)ws + ((n * 8 + 255) & ~(size_t)255));
-    hipError_t e = launch_lut_build_ws(coeffs, rows, detectors, levels, lut, planes, heads, stream);
+    hipError_t e = launch_lut_build_ws(coeffs, rows, detectors, levels, lut, planes, heads,
+                                       di->xcds, stream);
     return e == hipSuccess ? RC_OK : hip_fail(e);
 }
 

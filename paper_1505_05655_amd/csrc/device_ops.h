@@ -19,20 +19,21 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // LUT entry for integer level v (§I LUT generation, definition in rc.h):
 // Horner from the cubic coefficient down, one rounding per operation, then
-// round half away from zero and clamp to [0, L-1]. `lim` is (double)L.
-// The rounding and clamp are done as: c = min(max(acc, 0), L) in binary64
-// (maxNum sends NaN to 0, -Inf and every negative to 0, +Inf to L), then
-// r = trunc(c + h) with h = 0.5 - 2^-54 (the double just below 1/2), then
-// min(r, L-1). For 0 <= c < 2^52, trunc(fl(c + h)) is round-half-away(c):
-// if frac(c) >= 1/2 the exact sum is at least n - 2^-54 for n = ceil(c), and
-// it only falls below n when c = n - 1/2, where n - 2^-54 rounds up to n
-// (a tie to even at n = 1, nearer n above); if frac(c) < 1/2 the exact sum
-// is at most floor(c) + 1 - ulp(c) - 2^-54, more than half an ulp below
-// floor(c) + 1, so it cannot round up to it. With plain 1/2 instead of h,
-// c = 1/2 - 2^-54 would round to 1.
-__device__ __forceinline__ uint32_t lut_entry(double a0, double a1, double a2, double a3, int v,
-                                              double lim) {
-    const double x = (double)v;
+// round half away from zero and clamp to [0, L-1]; top is L-1.
+// The rounding and clamp are done as r = cvt(acc + h) with h = 0.5 - 2^-54
+// (the double just below 1/2) and v_cvt_u32_f64, which truncates, sends NaN,
+// -Inf and every negative to 0 and +Inf and everything above 2^32 to 2^32 - 1,
+// then min(r, L-1). For 0 <= acc < 2^52, trunc(fl(acc + h)) is
+// round-half-away(acc): if frac(acc) >= 1/2 the exact sum is at least n -
+// 2^-54 for n = ceil(acc), and it only falls below n when acc = n - 1/2, where
+// n - 2^-54 rounds up to n (a tie to even at n = 1, nearer n above); if
+// frac(acc) < 1/2 the exact sum is at most floor(acc) + 1 - ulp(acc) - 2^-54,
+// more than half an ulp below floor(acc) + 1, so it cannot round up to it.
+// With plain 1/2 instead of h, acc = 1/2 - 2^-54 would round to 1. For acc >=
+// 2^52 both the rounded value and r exceed every L; for acc < 0 the sum is
+// below 1, so r = 0.
+__device__ __forceinline__ uint32_t lut_round(double a0, double a1, double a2, double a3,
+                                              double x) {
     double acc = a3;
     acc = acc * x;
     acc = acc + a2;
@@ -40,10 +41,35 @@ __device__ __forceinline__ uint32_t lut_entry(double a0, double a1, double a2, d
     acc = acc + a1;
     acc = acc * x;
     acc = acc + a0;
-    const double c = __builtin_fmin(__builtin_fmax(acc, 0.0), lim);
-    const uint32_t r = (uint32_t)(c + 0x1.fffffffffffffp-2);
-    const uint32_t top = (uint32_t)lim - 1u;
-    return r < top ? r : top;
+    const double sum = acc + 0x1.fffffffffffffp-2;
+    uint32_t r;
+    // As an instruction: the C++ conversion is undefined out of range, and the
+    // saturation replaces a maximum and a minimum in binary64.
+    asm("v_cvt_u32_f64 %0, %1" : "=v"(r) : "v"(sum));
+    return r;
+}
+
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
+// Entries of two consecutive levels, packed: the conversion to 16 bits
+// saturates, then one packed minimum with top in both halves.
+__device__ __forceinline__ uint32_t lut_pair(double a0, double a1, double a2, double a3, double x0,
+                                             double x1, uint32_t top2) {
+    const uint32_t p = __builtin_bit_cast(
+        uint32_t, __builtin_amdgcn_cvt_pk_u16(lut_round(a0, a1, a2, a3, x0),
+                                              lut_round(a0, a1, a2, a3, x1)));
+    return __builtin_bit_cast(uint32_t,
+                              __builtin_elementwise_min(__builtin_bit_cast(u16x2, p),
+                                                        __builtin_bit_cast(u16x2, top2)));
+}
+
+// The 8 entries of levels x[0] .. x[7], two per word.
+__device__ __forceinline__ u32x4 lut_eight(double a0, double a1, double a2, double a3,
+                                           const double (&x)[8], uint32_t top2) {
+    return u32x4{lut_pair(a0, a1, a2, a3, x[0], x[1], top2),
+                 lut_pair(a0, a1, a2, a3, x[2], x[3], top2),
+                 lut_pair(a0, a1, a2, a3, x[4], x[5], top2),
+                 lut_pair(a0, a1, a2, a3, x[6], x[7], top2)};
 }
 
 // Workgroups are dispatched round-robin over the XCDs (block i runs on XCD
@@ -375,114 +401,224 @@ __device__ __forceinline__ uint32_t g_dense_checked(uint32_t dnv, uint32_t top, 
     return clamp0(u, (int)top);
 }
 
-// Encodes block `blk` (n entries, 1..64) of a LUT row: e holds the entries
-// two per word (entry 2k in the low half of e[k]). Returns false when the
-// block is not encodable.
-__device__ __forceinline__ bool dense_encode(const uint32_t (&e)[32], int n, uint32_t top, int blk,
-                                             uint64_t* plane, int16_t* head) {
-    auto at = [&](int i) -> int { return (int)((e[i >> 1] >> ((i & 1) * 16)) & 0xffffu); };
-    // Pass 1: smallest and largest step.
-    int mn = 1 << 20, mx = -(1 << 20);
-#pragma unroll
-    for (int t = 0; t < 63; ++t) {
-        if (t + 1 < n) {
-            const int st = at(t + 1) - at(t);
-            mn = min(mn, st);
-            mx = max(mx, st);
-        }
-    }
-    if (n > 1 && mn < 0) return false;  // decreasing somewhere
-    const int e0 = at(0), elast = at(n - 1);
-    // b: bit t+1 = b_t (the step-minus-slope bits, t = 0..62).
-    uint32_t lo = 0, hi = 0;
-    int s = 0, u0 = 0;
-    if (n == 1 || e0 == (int)top || elast == 0) {
-        // Constant (a single entry, all L-1, or all 0 in a non-decreasing block).
-        u0 = e0;
-    } else if (e0 != 0 && elast != (int)top) {
-        // No saturated entry (non-decreasing, 0 < e0, e_last < L-1). Any
-        // s in [mx - 1, mn] holds the steps; the largest keeps s <= 1 for
-        // the most blocks.
-        s = max(0, mx - 1);
-        if (s > 1 || mn < s) return false;
-        u0 = e0;
-#pragma unroll
-        for (int t = 0; t < 63; ++t) {
-            if (t + 1 < n) {
-                const uint32_t b = (uint32_t)(at(t + 1) - at(t) - s);
-                if (t + 1 < 32) lo |= b << (t + 1);
-                else hi |= b << (t + 1 - 32);
-            }
-        }
-    } else {
-        // A saturation transition inside the block. Steps between two
-        // unsaturated entries (the step out of a run of 0 and into a run of
-        // L-1 included) set the slope; steps inside a saturated run are s + 1.
-        int smin = 1 << 20, smax = -(1 << 20), first = n;
-#pragma unroll
-        for (int t = 0; t < 63; ++t) {
-            if (t + 1 < n) {
-                const int a = at(t), b = at(t + 1);
-                if (b != 0 && a != (int)top) {
-                    smin = min(smin, b - a);
-                    smax = max(smax, b - a);
-                }
-                if (a == 0 && b != 0 && first == n) first = t + 1;
-            }
-        }
-        s = max(0, smax - 1);
-        if (s > 1 || smin < s) return false;
-        // U_{first-1} = 0 when the block opens with a run of 0.
-        u0 = e0 != 0 ? e0 : -(s + 1) * (first - 1);
-#pragma unroll
-        for (int t = 0; t < 63; ++t) {
-            if (t + 1 < n) {
-                const int a = at(t), b = at(t + 1);
-                const uint32_t bit = (b != 0 && a != (int)top) ? (uint32_t)(b - a - s) : 1u;
-                if (t + 1 < 32) lo |= bit << (t + 1);
-                else hi |= bit << (t + 1 - 32);
-            }
-        }
-    }
-    const uint64_t bits = ((uint64_t)hi << 32) | lo;
-    // Bit t+1 of `bits` -> bit 63-t, complemented; bit 0 <- s.
-    const uint64_t z = (~(__builtin_bitreverse64(bits) << 1) & ~(uint64_t)1) | (uint64_t)s;
-    const int H = u0 + __builtin_popcountll(bits) - 63 - 64 * (s + 1) * blk - s;
-    if (H <= (int)kDenseBad || H > 32767) return false;
-    *plane = z;
-    *head = (int16_t)H;
-    return true;
+// Lane exchanges inside groups of 8 lanes as DPP moves (VALU, no LDS):
+// quad_perm [1,0,3,2] and [2,3,0,1] swap with the lane at distance 1 and 2,
+// row_half_mirror (lane i <-> 7 - i) with one of the other quad, and
+// row_shl:1 reads the next lane of the 16-lane row.
+constexpr int kDppQuadXor1 = 0xB1;
+constexpr int kDppQuadXor2 = 0x4E;
+constexpr int kDppHalfMirror = 0x141;
+constexpr int kDppRowShl1 = 0x101;
+
+template <int CTRL>
+__device__ __forceinline__ int dpp_move(int x) {
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, false);
 }
 
-// Encodes block `blk` of LUT row `row` (L levels) into *plane and *head; a
-// block that does not fit the dense form gets the header kDenseBad.
-__device__ __forceinline__ void dense_encode_row_block(const uint16_t* row, int L, int blk,
-                                                      bool vec16, uint64_t* plane, int16_t* head) {
-    const uint16_t* src = row + (size_t)blk * 64;
-    const int cnt = min(64, L - blk * 64);
-    uint32_t e[32];
-    if (vec16 && cnt == 64) {
-#pragma unroll
-        for (int q4 = 0; q4 < 8; ++q4) {
-            const u32x4 w = *(const u32x4*)(src + q4 * 8);
-            e[q4 * 4 + 0] = w.x;
-            e[q4 * 4 + 1] = w.y;
-            e[q4 * 4 + 2] = w.z;
-            e[q4 * 4 + 3] = w.w;
-        }
+// Sum / OR over the 8 lanes of x's group, returned on all 8.
+__device__ __forceinline__ uint32_t group8_add(uint32_t x) {
+    x += (uint32_t)dpp_move<kDppQuadXor1>((int)x);
+    x += (uint32_t)dpp_move<kDppQuadXor2>((int)x);
+    return x + (uint32_t)dpp_move<kDppHalfMirror>((int)x);
+}
+__device__ __forceinline__ uint32_t group8_or(uint32_t x) {
+    x |= (uint32_t)dpp_move<kDppQuadXor1>((int)x);
+    x |= (uint32_t)dpp_move<kDppQuadXor2>((int)x);
+    return x | (uint32_t)dpp_move<kDppHalfMirror>((int)x);
+}
+
+// ---- dense encoding of LUT rows by a wave ----------------------------------------------
+//
+// A wave takes 512 consecutive levels of a row per pass, 8 blocks of 64: lane
+// 8g + q holds entries 8q .. 8q + 7 of block g, two per word, so a pass loads
+// or stores 1 KiB of the row contiguously. The 8 lanes of a block decide its
+// form together with DPP moves (VALU, no LDS).
+
+// Both halves of a word at a time (16-bit entries, steps and flags).
+__device__ __forceinline__ uint32_t pk_sub(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, a) -
+                                                __builtin_bit_cast(u16x2, b)));
+}
+__device__ __forceinline__ uint32_t pk_add(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, a) +
+                                                __builtin_bit_cast(u16x2, b)));
+}
+__device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a),
+                                                                  __builtin_bit_cast(u16x2, b)));
+}
+
+// The step bits x0 .. x3 of a lane (bit 0 of each half), as one byte.
+__device__ __forceinline__ uint32_t step_byte(uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3,
+                                              int q) {
+    const uint32_t y = x0 | (x1 << 2) | (x2 << 4) | (x3 << 6);
+    return (y | (y >> 15)) & (q == 7 ? 0x7Fu : 0xFFu);
+}
+
+// Bit k of the steps of a packed block's four lanes q = 0 .. 3 (8 steps each,
+// two per word), as the block's plane on all four.
+__device__ __forceinline__ uint32_t quad_plane(uint32_t d0, uint32_t d1, uint32_t d2, uint32_t d3,
+                                               int k, int q) {
+    constexpr uint32_t kOnes = 0x00010001u;
+    const uint32_t y = ((d0 >> k) & kOnes) | (((d1 >> k) & kOnes) << 2) |
+                       (((d2 >> k) & kOnes) << 4) | (((d3 >> k) & kOnes) << 6);
+    uint32_t word = ((y | (y >> 15)) & 0xFFu) << (q << 3);
+    word |= (uint32_t)dpp_move<kDppQuadXor1>((int)word);
+    return word | (uint32_t)dpp_move<kDppQuadXor2>((int)word);
+}
+
+// Blocks (of a group of 8 lanes) in which no lane fails.
+__device__ __forceinline__ bool group8_ok(bool fail, int lane) {
+    const uint64_t f = __ballot(fail);
+    return f == 0 || ((f >> (lane & 56)) & 0xFFu) == 0;
+}
+
+// One pass of one row: the plane word and header (kDenseBad if the block does
+// not fit) of block blk, valid on lane q = 0. whole: the pass lies inside the
+// row (wave-uniform). Bound by instruction issue, so it works on two entries
+// per word, without a branch per entry: the 8 steps of a lane in 4 packed
+// subtractions; a block's slope s is 1 if any of its steps has bit 1 set;
+// every step minus s must then be 0 or 1 in both halves (a negative or larger
+// step fails that), and those bits are the block's. The usual pass is whole
+// with all entries in 1 .. L-2 (a lane's are if its first is not 0 or above
+// L-1 and its last is below L-1, or it has a negative step and the block fails
+// either way): about 45 instructions. The other kind masks the steps that say
+// nothing about the slope (inside a run of 0 or of L-1, or past the row; they
+// must be 0 and count as s + 1): about 100. With one entry per register and a
+// branch per entry the two took 110 and 500, and the build with encoding 80 us
+// on 3 x 6000 rows of 4096 levels against @@WS@@ us now.
+__device__ __forceinline__ void encode_pass(const u32x4 w, int L, int blk, bool whole,
+                                            uint64_t* z_out, int16_t* head_out) {
+    constexpr uint32_t kOnes = 0x00010001u;
+    const int lane = (int)(threadIdx.x & 63);
+    const int q = lane & 7;
+    const uint32_t top = (uint32_t)(L - 1);
+    // Steps e_{k+1} - e_k, k = 2i and 2i + 1 in word i; b_i are the later entries.
+    const uint32_t nx = (uint32_t)dpp_move<kDppRowShl1>((int)w.x);  // lane q + 1's (q < 7)
+    const uint32_t b0 = __builtin_amdgcn_alignbit(w.y, w.x, 16);
+    const uint32_t b1 = __builtin_amdgcn_alignbit(w.z, w.y, 16);
+    const uint32_t b2 = __builtin_amdgcn_alignbit(w.w, w.z, 16);
+    const uint32_t b3 = __builtin_amdgcn_alignbit(nx, w.w, 16);
+    const uint32_t d0 = pk_sub(b0, w.x), d1 = pk_sub(b1, w.y), d2 = pk_sub(b2, w.z);
+    const uint32_t d3 = pk_sub(b3, w.w);
+    const uint32_t first = w.x & 0xffffu, last = w.w >> 16;
+    int s, u0 = (int)first;  // lane q = 0: the block's first entry
+    bool ok;
+    uint32_t lo8;
+    if (whole && !__any(first - 1u >= top || last >= top)) {
+        // Lane q = 7 has no step 63: it repeats its step 62.
+        const uint32_t e3 = __builtin_amdgcn_perm(d3, d3, q == 7 ? 0x01000100u : 0x03020100u);
+        const uint32_t any = d0 | d1 | d2 | e3;
+        const uint32_t two = group8_or((any | (any >> 16)) & 2u);
+        s = (int)(two >> 1);
+        const uint32_t ss = (two >> 1) | (two << 15);
+        const uint32_t x0 = pk_sub(d0, ss), x1 = pk_sub(d1, ss), x2 = pk_sub(d2, ss);
+        const uint32_t x3 = pk_sub(e3, ss);
+        ok = group8_ok(((x0 | x1 | x2 | x3) & ~kOnes) != 0, lane);
+        lo8 = step_byte(x0, x1, x2, x3, q);
     } else {
+        // Valid steps of this lane (entries t and t + 1 both in the block).
+        const int v = min(64, L - (blk << 6)) - 1 - (q << 3);
+        auto valid = [&](int i) {
+            return v >= 2 * i + 2 ? 0xFFFFFFFFu : (v == 2 * i + 1 ? 0xFFFFu : 0u);
+        };
+        const uint32_t b[4] = {b0, b1, b2, b3}, d[4] = {d0, d1, d2, d3};
+        const uint32_t top2 = top * kOnes;
+        uint32_t m[4], any = 0, zeros = 0, wrong = 0;
 #pragma unroll
-        for (int k = 0; k < 32; ++k) {
-            const uint32_t a = 2 * k < cnt ? src[2 * k] : 0u;
-            const uint32_t c = 2 * k + 1 < cnt ? src[2 * k + 1] : 0u;
-            e[k] = a | (c << 16);
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t vm = valid(i);
+            const uint32_t up = pk_min(b[i], kOnes);  // 1 where the later entry is not 0
+            // All ones where the step tells the slope.
+            m[i] = pk_sub(0u, up & pk_min(pk_sub(top2, w[i]), kOnes)) & vm;
+            any |= d[i] & m[i];
+            wrong |= d[i] & ~m[i] & vm;
+            zeros = pk_add(zeros, (kOnes - up) & vm);
+        }
+        const uint32_t two = group8_or((any | (any >> 16)) & 2u);
+        s = (int)(two >> 1);
+        const uint32_t ss = (two >> 1) | (two << 15);
+        uint32_t x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            x[i] = (pk_sub(d[i], ss) & m[i]) | (kOnes & ~m[i]);
+            wrong |= x[i] & ~kOnes;
+        }
+        ok = group8_ok(wrong != 0 || first > top || last > top, lane);
+        lo8 = step_byte(x[0], x[1], x[2], x[3], q);
+        // A block that opens with zeros: as many steps below 0 as steps end in 0.
+        const int nz = (int)group8_add((zeros & 0xffffu) + (zeros >> 16));
+        if (u0 == 0) u0 = -(s + 1) * nz;
+    }
+    // Plane word: bit 63 - t = 1 - b_t, bit 0 = s. Lane q holds steps 8q .. 8q
+    // + 7: its byte, bit-reversed, belongs in the high word for q < 4 (byte 3 -
+    // q), in the low one for q >= 4 (byte 7 - q); each quad ORs its word.
+    uint32_t word = __builtin_bitreverse32(lo8) >> ((q & 3) << 3);
+    word |= (uint32_t)dpp_move<kDppQuadXor1>((int)word);
+    word |= (uint32_t)dpp_move<kDppQuadXor2>((int)word);
+    const uint32_t hi = word, lo = (uint32_t)dpp_move<kDppHalfMirror>((int)word);  // q = 0
+    const int H = u0 + __builtin_popcount(hi) + __builtin_popcount(lo) - 63 - ((s + 1) << 6) * blk -
+                  s;
+    if (H <= (int)kDenseBad || H > 32767) ok = false;
+    const uint64_t z = ((uint64_t)~hi << 32) | (uint64_t)((~lo & ~1u) | (uint32_t)s);
+    *z_out = ok ? z : 0;
+    *head_out = ok ? (int16_t)H : kDenseBad;
+}
+
+// All blocks of R rows of L levels: fetch(r, v0, whole, w) gives every row's 8
+// entries from level v0 of pass r (words past the row are ignored; several
+// rows per pass keep several loads in flight), put(i, blk, plane, header)
+// takes row i's block from lane q = 0. Every lane of the wave must call it.
+template <int R, typename F, typename P>
+__device__ __forceinline__ void encode_rows(int L, F fetch, P put) {
+    const int NB = (L + 63) >> 6;
+    const int lane = (int)(threadIdx.x & 63);
+    for (int r = 0; r < ((NB + 7) >> 3); ++r) {
+        const int blk = (r << 3) + (lane >> 3);
+        const bool whole = ((r + 1) << 9) <= L;
+        u32x4 w[R];
+        fetch((r << 9) + (lane << 3), whole, w);
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            uint64_t z;
+            int16_t h;
+            encode_pass(w[i], L, blk, whole, &z, &h);
+            if ((lane & 7) == 0 && blk < NB) put(i, blk, z, h);
         }
     }
-    uint64_t pl = 0;
-    int16_t hd = kDenseBad;
-    if (!dense_encode(e, cnt, (uint32_t)(L - 1), blk, &pl, &hd)) hd = kDenseBad;
-    *plane = pl;
-    *head = hd;
+}
+
+// Entries [v0, v0 + 8) of a LUT row in global memory, those past the row 0
+// (vec16: the row's 16-byte groups are aligned and whole).
+__device__ __forceinline__ u32x4 load_lut8(const uint16_t* row, int v0, int L, bool whole,
+                                           bool vec16) {
+    if (vec16) return whole || v0 < L ? *(const u32x4*)(row + v0) : u32x4{0u, 0u, 0u, 0u};
+    u32x4 w;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t a = v0 + 2 * i < L ? row[v0 + 2 * i] : 0u;
+        const uint32_t b = v0 + 2 * i + 1 < L ? row[v0 + 2 * i + 1] : 0u;
+        w[i] = a | (b << 16);
+    }
+    return w;
+}
+
+// The doubles v0 .. v0 + 7.
+__device__ __forceinline__ void levels8(int v0, double (&x)[8]) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = (double)(v0 + k);
+}
+
+// Writes the first n of the 8 entries w of a LUT row to dst: one 16-byte store
+// when they are whole and aligned (non-temporal if nt), else 16-bit stores.
+__device__ __forceinline__ void store_lut8(uint16_t* dst, const u32x4 w, int n, bool vec16,
+                                           bool nt) {
+    if (vec16 && n >= 8) {
+        if (nt) __builtin_nontemporal_store(w, (u32x4*)dst);
+        else *(u32x4*)dst = w;
+    } else {
+        for (int k = 0; k < min(n, 8); ++k) dst[k] = (uint16_t)(w[k >> 1] >> ((k & 1) * 16));
+    }
 }
 
 // Blocks of a dense strip the form cannot hold, summed over the workgroup
@@ -535,12 +671,15 @@ __device__ __forceinline__ int packed_any(int flag, u32x2* planes) {
 // Lanes own VEC adjacent detectors of one line; q consecutive threads cover
 // a line of the strip and the workgroup walks floor(blockDim.x / q) lines at
 // a time. q = W / VEC (`dense` false: a wave covers whole line segments when
-// q divides 64, lanes past a narrower strip idle) or weff / VEC (`dense`
-// true: no idle lanes inside a wave). Requirements (checked on the host): W = 2^logW >= weff, VEC | W,
-// VEC | weff, VEC | d0, VEC | D, image pointers aligned to 2*VEC bytes,
-// W / VEC <= blockDim.x, and the LDS size of the mode for W detectors. dn and
-// out may be the same buffer (in place): every pixel is read and then written
-// by the same lane, so they are deliberately not __restrict__.
+// q divides 64, lanes past a narrower strip idle) or ceil(weff / VEC) (`dense`
+// true: no idle lanes inside a wave). If VEC does not divide weff (`dense`
+// only), the last lane of a line takes the strip's last VEC detectors, some of
+// which the lane before it takes too; both write the same values, so dn and
+// out must then not be the same buffer. Requirements (checked on the host): W
+// = 2^logW >= weff >= VEC, image pointers aligned to 2 bytes, W / VEC <=
+// blockDim.x, and the LDS size of the mode for W detectors. dn and out may be
+// the same buffer (in place) when VEC | weff: every pixel is read and then
+// written by the same lane, so they are deliberately not __restrict__.
 // LANE_ENCODE: the dense mode may encode its strip from the global LUT
 // (false: the caller always passes a pre-encoded strip, and the encoder is
 // not compiled in).
@@ -560,7 +699,12 @@ __device__ __forceinline__ void apply_tile(const uint16_t* dn, const uint16_t* _
     const size_t Lz = (size_t)L;
     const uint16_t* strip_lut = lut + ((size_t)b * (size_t)D + (size_t)d0) * Lz;
     const int logq = logW - LOGVEC;  // LDS positions per VEC slot = W / VEC
-    const int q = dense ? (weff >> LOGVEC) : (1 << logq);  // lanes per strip line
+    // Lanes per strip line, and the strip's LDS positions: position (k, ln), at
+    // p = (k << logq) + ln, holds detector pos_detector(k, ln), the k-th pixel
+    // of lane ln.
+    const int lanes = (weff + VEC - 1) >> LOGVEC;
+    const int q = dense ? lanes : (1 << logq);
+    auto pos_detector = [&](int k, int ln) { return min(ln << LOGVEC, weff - VEC) + k; };
     const int row = tid / q;         // this thread's line within a pass
     const int lane = tid - row * q;
     // Lines per pass, from the nst streaming threads (0: all of them).
@@ -568,8 +712,8 @@ __device__ __forceinline__ void apply_tile(const uint16_t* dn, const uint16_t* _
     // would otherwise wrap every buffer access in a waterfall loop).
     const int rpp = __builtin_amdgcn_readfirstlane((nst ? nst : nt) / q);
     // Threads past the last whole line, or past the strip, only stage.
-    const bool streams = row < rpp && lane * VEC < weff;
-    const int j = lane * VEC;
+    const bool streams = row < rpp && lane < lanes;
+    const int j = pos_detector(0, lane);
     // The tile's image bytes as buffer resources: line n0, detector d0 is at
     // byte 0; the range ends after the tile's last pixel.
     const size_t tile0 = ((size_t)b * (size_t)N + (size_t)n0) * (size_t)D + (size_t)d0;
@@ -655,53 +799,53 @@ __device__ __forceinline__ void apply_tile(const uint16_t* dn, const uint16_t* _
         if (pre_planes) {
             // Stage the blocks k_dense_encode wrote ([band][block][detector]):
             // consecutive threads read consecutive detectors of one block.
-            const int items = NB * weff;
+            const int wpos = lanes << LOGVEC;
+            const int items = NB * wpos;
             const size_t row0 = (size_t)b * (size_t)NB * (size_t)D + (size_t)d0;
             for (int it = tid; it < items; it += nt) {
-                const int blk = it / weff;
-                const int jj = it - blk * weff;
-                const size_t g = row0 + (size_t)blk * (size_t)D + (size_t)jj;
+                const int blk = it / wpos;
+                const int i = it - blk * wpos;
+                const int k = i & (VEC - 1), ln = i >> LOGVEC;
+                const size_t g = row0 + (size_t)blk * (size_t)D + (size_t)pos_detector(k, ln);
                 const int16_t hd = pre_heads[g];
-                const int p = ((jj & (VEC - 1)) << logq) + (jj >> LOGVEC);
+                const int p = (k << logq) + ln;
                 bad += (int)(hd == kDenseBad);
                 planes[(blk << logW) + p] = pre_planes[g];
                 heads[(blk << logW) + p] = hd;
             }
         }
-        // Stage: one lane encodes one block (detector jj, 64 levels); a wave
-        // covers 64 consecutive LDS positions of one block index, so its
-        // plane and header writes are consecutive words.
-        const int units = (!LANE_ENCODE || pre_planes) ? 0 : NB << logW;
-        for (int u = tid; LANE_ENCODE && u < units; u += nt) {
-            const int blk = u >> logW;
-            const int p = u & (W - 1);
-            const int jj = ((p & ((1 << logq) - 1)) << LOGVEC) + (p >> logq);
-            if (jj >= weff) continue;
-            const uint16_t* src = strip_lut + (size_t)jj * Lz + (size_t)blk * 64;
-            const int cnt = min(64, L - blk * 64);
-            uint32_t e[32];
-            if (lut_vec && cnt == 64) {
+        // Stage: a wave encodes kRows rows of the strip at a time (the loads of
+        // a pass of all of them in flight together).
+        if (LANE_ENCODE && !pre_planes) {
+            constexpr int kRows = 4;
+            const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), nwv = nt >> 6;
+            for (int j0 = wv * kRows; j0 < weff; j0 += nwv * kRows) {
+                encode_rows<kRows>(
+                    L,
+                    [&](int v0, bool whole, u32x4 (&w)[kRows]) {
 #pragma unroll
-                for (int q4 = 0; q4 < 8; ++q4) {
-                    const u32x4 w = *(const u32x4*)(src + q4 * 8);
-                    e[q4 * 4 + 0] = w.x;
-                    e[q4 * 4 + 1] = w.y;
-                    e[q4 * 4 + 2] = w.z;
-                    e[q4 * 4 + 3] = w.w;
-                }
-            } else {
-#pragma unroll
-                for (int k = 0; k < 32; ++k) {
-                    const uint32_t a = 2 * k < cnt ? src[2 * k] : 0u;
-                    const uint32_t b = 2 * k + 1 < cnt ? src[2 * k + 1] : 0u;
-                    e[k] = a | (b << 16);
-                }
+                        for (int i = 0; i < kRows; ++i)
+                            w[i] = load_lut8(strip_lut + (size_t)min(j0 + i, weff - 1) * Lz, v0, L,
+                                             whole, lut_vec);
+                    },
+                    [&](int i, int blk, uint64_t z, int16_t h) {
+                        const int jj = j0 + i;
+                        if (jj >= weff) return;
+                        bad += (int)(h == kDenseBad);
+                        // Its position among the whole lanes, and in the last.
+                        const int k = jj - (weff - VEC);
+                        if ((jj >> LOGVEC) < lanes - 1) {
+                            const int p = ((jj & (VEC - 1)) << logq) + (jj >> LOGVEC);
+                            planes[(blk << logW) + p] = z;
+                            heads[(blk << logW) + p] = h;
+                        }
+                        if (k >= 0) {
+                            const int p = (k << logq) + lanes - 1;
+                            planes[(blk << logW) + p] = z;
+                            heads[(blk << logW) + p] = h;
+                        }
+                    });
             }
-            uint64_t pl = 0;
-            int16_t hd = kDenseBad;
-            if (!dense_encode(e, cnt, top, blk, &pl, &hd)) ++bad;
-            planes[u] = pl;
-            heads[u] = hd;
         }
         const uint32_t nbad = dense_bad_blocks(bad, planes, heads);
         if (nbad == 0) {
@@ -729,15 +873,15 @@ __device__ __forceinline__ void apply_tile(const uint16_t* dn, const uint16_t* _
             const int gtid = tid - grp * per;
             const int grow = gtid / q;
             const int glane = gtid - grow * q;
-            const int gj = glane * VEC;
+            const int gj = pos_detector(0, glane);
             const uint32_t gvo = (uint32_t)(((size_t)grow * (size_t)D + (size_t)gj) * 2) +
                                  (uint32_t)ci * pass_bytes + (uint32_t)grp * pass_adv;
             const uint32_t gadv = (uint32_t)ng * pass_adv;
             const int gpasses = grp < passes ? (passes - grp + ng - 1) / ng : 0;
             const uint16_t* lrow = strip_lut + (size_t)gj * Lz;
-            if (grp >= ng || grow >= rpp || gj >= weff || gpasses == 0) {
+            if (grp >= ng || grow >= rpp || glane >= lanes || gpasses == 0) {
                 // nothing to stream
-            } else if (nbad <= (uint32_t)NB) {
+            } else if (LANE_ENCODE && nbad <= (uint32_t)NB) {
                 // Few: decode every pixel and keep the smallest header the
                 // lane read in each line; a lane that met such a block then
                 // takes those pixels from the LUT row. One branch per
@@ -797,8 +941,9 @@ __device__ __forceinline__ void apply_tile(const uint16_t* dn, const uint16_t* _
             // Stage, coalesced and bank-conflict free: a wave packs 16
             // consecutive LDS positions of one level block. Lane 4g+q loads
             // the q-th 16-byte quarter (8 entries) of the block's row for
-            // position p0+g; the four quarters' steps are merged by lane
-            // shuffles and lane 4g writes the block's words.
+            // position p0+g; the steps are formed two per word (see
+            // encode_pass), the four quarters' bits are merged by DPP moves
+            // and lane 4g writes the block's words.
             const int wl = tid & 63, wv = tid >> 6, nwv = nt >> 6;
             const int g = wl >> 2, q = wl & 3;
             const int logpg = logW - 4;
@@ -812,9 +957,10 @@ __device__ __forceinline__ void apply_tile(const uint16_t* dn, const uint16_t* _
                 for (int s = 0; s < SU; ++s) {
                     const int u = u0 + s * nwv;
                     const int p = ((u & ((1 << logpg) - 1)) << 4) + g;
-                    const int jj = ((p & ((1 << logq) - 1)) << LOGVEC) + (p >> logq);
+                    const int ln = p & ((1 << logq) - 1);
+                    const int jj = pos_detector(p >> logq, ln);
                     qv[s] = u32x4{0u, 0u, 0u, 0u};
-                    if (u < units && jj < weff) {
+                    if (u < units && ln < lanes) {
                         qv[s] = *(const u32x4*)(strip_lut + (size_t)jj * Lz +
                                                 (size_t)(u >> logpg) * 32 + q * 8);
                     }
@@ -825,46 +971,40 @@ __device__ __forceinline__ void apply_tile(const uint16_t* dn, const uint16_t* _
                     if (u >= units) break;  // uniform across the wave
                     const int blk = u >> logpg;
                     const int p = ((u & ((1 << logpg) - 1)) << 4) + g;
-                    const int jj = ((p & ((1 << logq) - 1)) << LOGVEC) + (p >> logq);
-                    const bool valid = jj < weff;
-                    const u32x4 v4 = qv[s];
-                    const uint32_t e[8] = {v4.x & 0xffffu, v4.x >> 16, v4.y & 0xffffu,
-                                           v4.y >> 16,     v4.z & 0xffffu, v4.z >> 16,
-                                           v4.w & 0xffffu, v4.w >> 16};
-                    const uint32_t nxt = (uint32_t)__shfl_down((int)e[0], 1, 64);
-                    uint32_t lo8 = 0, hi8 = 0, over = 0;
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        // Step from entry 8q+i to 8q+i+1; block step 31 does not exist.
-                        const uint32_t step =
-                            i < 7 ? e[i + 1] - e[i] : (q < 3 ? nxt - e[7] : 0u);
-                        over |= step > 3u;
-                        lo8 |= (step & 1u) << i;
-                        hi8 |= ((step >> 1) & 1u) << i;
-                    }
-                    uint32_t lo = lo8 << (q * 8), hi = hi8 << (q * 8);
-                    lo |= (uint32_t)__shfl_xor((int)lo, 1, 64);
-                    hi |= (uint32_t)__shfl_xor((int)hi, 1, 64);
-                    lo |= (uint32_t)__shfl_xor((int)lo, 2, 64);
-                    hi |= (uint32_t)__shfl_xor((int)hi, 2, 64);
-                    if (valid) {
-                        bad |= (int)over;
-                        if (q == 0) {
-                            u32x2 pl;
-                            pl.x = lo;
-                            pl.y = hi;
-                            planes[blk * W + p] = pl;
-                            bases[blk * W + p] = (uint16_t)e[0];
-                        }
+                    const bool valid = (p & ((1 << logq) - 1)) < lanes;
+                    const u32x4 w = qv[s];
+                    const uint32_t nx = (uint32_t)dpp_move<kDppRowShl1>((int)w.x);
+                    const uint32_t d0 = pk_sub(__builtin_amdgcn_alignbit(w.y, w.x, 16), w.x);
+                    const uint32_t d1 = pk_sub(__builtin_amdgcn_alignbit(w.z, w.y, 16), w.y);
+                    const uint32_t d2 = pk_sub(__builtin_amdgcn_alignbit(w.w, w.z, 16), w.z);
+                    // Block step 31 (lane q = 3) does not exist.
+                    const uint32_t d3 = pk_sub(__builtin_amdgcn_alignbit(nx, w.w, 16), w.w) &
+                                        (q == 3 ? 0xFFFFu : 0xFFFFFFFFu);
+                    // A step above 3 or negative; 16-bit steps of 0 .. 3 that
+                    // wrapped around leave the lane's last entry below its
+                    // first, or the next lane's first below its last.
+                    const bool over = ((d0 | d1 | d2 | d3) & 0xFFFCFFFCu) != 0 ||
+                                      (w.w >> 16) < (w.x & 0xffffu) ||
+                                      (q < 3 && (nx & 0xffffu) < (w.w >> 16));
+                    bad |= (int)(valid && over);
+                    uint32_t lo = quad_plane(d0, d1, d2, d3, 0, q);
+                    uint32_t hi = quad_plane(d0, d1, d2, d3, 1, q);
+                    if (valid && q == 0) {
+                        u32x2 pl;
+                        pl.x = lo;
+                        pl.y = hi;
+                        planes[blk * W + p] = pl;
+                        bases[blk * W + p] = (uint16_t)w.x;
                     }
                 }
             }
         } else {
             // Stage, general shapes: item = (detector jj, block), blocks fastest.
-            const int items = weff * NB;
+            const int items = (lanes << LOGVEC) * NB;
             for (int it = tid; it < items; it += nt) {
-                const int jj = it / NB;
-                const int blk = it - jj * NB;
+                const int i = it / NB;
+                const int blk = it - i * NB;
+                const int jj = pos_detector(i & (VEC - 1), i >> LOGVEC);
                 const uint16_t* src = strip_lut + (size_t)jj * Lz + (size_t)blk * 32;
                 const int cnt = min(32, L - blk * 32);
                 uint32_t e[32];
@@ -895,7 +1035,7 @@ __device__ __forceinline__ void apply_tile(const uint16_t* dn, const uint16_t* _
                         hi |= ((step >> 1) & 1u) << i;
                     }
                 }
-                const int p = ((jj & (VEC - 1)) << logq) + (jj >> LOGVEC);
+                const int p = ((i & (VEC - 1)) << logq) + (i >> LOGVEC);
                 u32x2 pl;
                 pl.x = lo;
                 pl.y = hi;
@@ -924,32 +1064,6 @@ __device__ __forceinline__ void apply_tile(const uint16_t* dn, const uint16_t* _
 
 // ---- fused LUT build + correction (batched requests) ------------------------------------
 
-// Writes entries [v0, v0 + n) of one LUT row (n <= 8, values in e) to global
-// memory: one 16-byte non-temporal store when the 8 entries are aligned (the
-// tile reads its LUT from LDS, not back from memory), else 16-bit stores.
-__device__ __forceinline__ void store_lut8(uint16_t* dst, const uint32_t* e, int n, bool vec16) {
-    if (vec16 && n == 8) {
-        u32x4 q;
-        q.x = e[0] | (e[1] << 16);
-        q.y = e[2] | (e[3] << 16);
-        q.z = e[4] | (e[5] << 16);
-        q.w = e[6] | (e[7] << 16);
-        __builtin_nontemporal_store(q, (u32x4*)dst);
-    } else {
-        for (int k = 0; k < n; ++k) dst[k] = (uint16_t)e[k];
-    }
-}
-
-// One LUT row encoded in the dense form by one wave: block blk's plane and
-// header go to planes[blk * stride] and heads[blk * stride] (the
-// [band][block][detector] layout of a dense workspace); a block the form
-// cannot hold gets the header kDenseBad. src.fetch(v0, n) gives the n <= 8
-// entries from level v0 packed two per word (evaluated from coefficients,
-// or read from a LUT row); with dst they are also written there (L entries). 8 blocks per
-// pass: lane 8g + q takes levels 64 (8 r + g) + 8q .. + 7, so a pass reads
-// or stores 1 KiB of the row contiguously; the 8 lanes of a block decide its
-// form (the cases of dense_encode) with xor-shuffles inside their group and
-// OR their step bits together. Every lane of the wave must call it.
 // Computes the LUT rows of band b, detectors [d0, d0 + weff) from their
 // calibration coefficients straight into the LDS tile (raw or packed layout,
 // as the correction tile reads them) and, if `write_lut`, also into the
@@ -963,7 +1077,7 @@ __device__ __forceinline__ int build_strip(const double* __restrict__ coeffs, ui
     const int W = 1 << logW;
     const int tid = threadIdx.x, nt = blockDim.x;
     const int logq = logW - LOGVEC;
-    const double lim = (double)L;
+    const uint32_t top2 = (uint32_t)(L - 1) * 0x00010001u;
     const size_t row0 = (size_t)b * (size_t)D + (size_t)d0;
     int bad = 0;
     if constexpr (MODE == kRaw) {
@@ -980,20 +1094,21 @@ __device__ __forceinline__ int build_strip(const double* __restrict__ coeffs, ui
             const double a0 = a[0], a1 = a[1], a2 = a[2], a3 = a[3];
             const int v0 = c * 8;
             const int n = min(8, L - v0);
-            uint32_t e[8];
+            double x[8];
+            levels8(v0, x);
+            const u32x4 w = lut_eight(a0, a1, a2, a3, x, top2);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                e[k] = k < n ? lut_entry(a0, a1, a2, a3, v0 + k, lim) : 0u;
-                if (k < n) tile[((v0 + k) << logW) + j] = (uint16_t)e[k];
-            }
-            if (write_lut) store_lut8(lut + (row0 + (size_t)j) * (size_t)L + v0, e, n, lut_vec);
+            for (int k = 0; k < 8; ++k)
+                if (k < n) tile[((v0 + k) << logW) + j] = (uint16_t)(w[k >> 1] >> ((k & 1) * 16));
+            if (write_lut) store_lut8(lut + (row0 + (size_t)j) * (size_t)L + v0, w, n, lut_vec, true);
         }
         __syncthreads();
     } else {
         // A wave evaluates one detector row at a time, 16 blocks of 32 levels
         // per pass: lane 4g + q computes levels 32 (16 r + g) + 8q .. + 7, so
         // the wave's global LUT stores cover 1 KiB of the row contiguously.
-        // The four lanes of a block merge their step bits by lane shuffles.
+        // The steps are formed two per word (see encode_pass) and the four
+        // lanes of a block merge their bits by DPP moves.
         const int NB = (L + 31) >> 5;
         u32x2* planes = (u32x2*)smem;
         uint16_t* bases = (uint16_t*)(planes + (size_t)NB * W);
@@ -1002,7 +1117,7 @@ __device__ __forceinline__ int build_strip(const double* __restrict__ coeffs, ui
         const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
         const int nwv = nt >> 6;
         const int rounds = (NB + 15) >> 4;
-        uint32_t maxstep = 0;
+        uint32_t wrong = 0;
         for (int j = wv; j < weff; j += nwv) {
             const double* a = coeffs + (row0 + (size_t)j) * 4;
             const double a0 = a[0], a1 = a[1], a2 = a[2], a3 = a[3];
@@ -1011,38 +1126,43 @@ __device__ __forceinline__ int build_strip(const double* __restrict__ coeffs, ui
             for (int r = 0; r < rounds; ++r) {
                 const int blk = (r << 4) + g;
                 const int v0 = (blk << 5) + (q << 3);
-                const int n = max(0, min(8, L - v0));
-                uint32_t e[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) e[k] = k < n ? lut_entry(a0, a1, a2, a3, v0 + k, lim) : 0u;
-                if (write_lut && n > 0) store_lut8(dst + v0, e, n, lut_vec);
+                double x[8];
+                levels8(v0, x);
+                const u32x4 w = lut_eight(a0, a1, a2, a3, x, top2);
+                if (write_lut && v0 < L) store_lut8(dst + v0, w, L - v0, lut_vec, true);
                 // Step i of a block (bit i of the planes) is entry i+1 minus
                 // entry i; a step that leaves the block or the row is 0.
-                const uint32_t nxt = (uint32_t)__shfl_down((int)e[0], 1, 64);
-                uint32_t lo8 = 0, hi8 = 0;
+                const uint32_t nx = (uint32_t)dpp_move<kDppRowShl1>((int)w.x);
+                uint32_t d[4] = {pk_sub(__builtin_amdgcn_alignbit(w.y, w.x, 16), w.x),
+                                 pk_sub(__builtin_amdgcn_alignbit(w.z, w.y, 16), w.y),
+                                 pk_sub(__builtin_amdgcn_alignbit(w.w, w.z, 16), w.z),
+                                 pk_sub(__builtin_amdgcn_alignbit(nx, w.w, 16), w.w)};
+                if (((r + 1) << 9) <= L) {
+                    d[3] &= q == 3 ? 0xFFFFu : 0xFFFFFFFFu;
+                } else {
+                    const int v = min(32, L - (blk << 5)) - 1 - (q << 3);  // valid steps
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const bool has = k < 7 ? k + 1 < n : (q < 3 && n == 8 && v0 + 8 < L);
-                    const uint32_t step = has ? (k < 7 ? e[k + 1] : nxt) - e[k] : 0u;
-                    maxstep = max(maxstep, step);  // wraps high when negative
-                    lo8 |= (step & 1u) << k;
-                    hi8 |= ((step >> 1) & 1u) << k;
+                    for (int i = 0; i < 4; ++i)
+                        d[i] &= v >= 2 * i + 2 ? 0xFFFFFFFFu : (v == 2 * i + 1 ? 0xFFFFu : 0u);
                 }
-                uint32_t lo = lo8 << (q << 3), hi = hi8 << (q << 3);
-                lo |= (uint32_t)__shfl_xor((int)lo, 1, 64);
-                hi |= (uint32_t)__shfl_xor((int)hi, 1, 64);
-                lo |= (uint32_t)__shfl_xor((int)lo, 2, 64);
-                hi |= (uint32_t)__shfl_xor((int)hi, 2, 64);
+                wrong |= d[0] | d[1] | d[2] | d[3];  // a step above 3 or negative
+                // (16-bit steps of 0 .. 3 that wrapped around leave a lower
+                // entry after a higher one; only levels above 65533 can.)
+                if (L > 65533 && v0 + 8 <= L)
+                    wrong |= ((w.w >> 16) < (w.x & 0xffffu) ||
+                              (q < 3 && v0 + 8 < L && (nx & 0xffffu) < (w.w >> 16))) ? 4u : 0u;
+                const uint32_t lo = quad_plane(d[0], d[1], d[2], d[3], 0, q);
+                const uint32_t hi = quad_plane(d[0], d[1], d[2], d[3], 1, q);
                 if (q == 0 && blk < NB) {
                     u32x2 pl;
                     pl.x = lo;
                     pl.y = hi;
                     planes[blk * W + p] = pl;
-                    bases[blk * W + p] = (uint16_t)e[0];
+                    bases[blk * W + p] = (uint16_t)w.x;
                 }
             }
         }
-        bad = packed_any(maxstep > 3u ? 1 : 0, planes);
+        bad = packed_any((wrong & 0xFFFCFFFCu) != 0 ? 1 : 0, planes);
     }
     return bad;
 }
@@ -1051,7 +1171,7 @@ __device__ __forceinline__ int build_strip(const double* __restrict__ coeffs, ui
 // strip that cannot be packed and whose tile did not write them already).
 __device__ __forceinline__ void write_strip(const double* __restrict__ coeffs, uint16_t* lut, int D,
                                             int L, int b, int d0, int weff, bool lut_vec) {
-    const double lim = (double)L;
+    const uint32_t top2 = (uint32_t)(L - 1) * 0x00010001u;
     const size_t row0 = (size_t)b * (size_t)D + (size_t)d0;
     const int chunks = (L + 7) >> 3;
     const int items = chunks * weff;
@@ -1060,10 +1180,10 @@ __device__ __forceinline__ void write_strip(const double* __restrict__ coeffs, u
         const int v0 = (it - j * chunks) * 8;
         const int n = min(8, L - v0);
         const double* a = coeffs + (row0 + (size_t)j) * 4;
-        uint32_t e[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) e[k] = k < n ? lut_entry(a[0], a[1], a[2], a[3], v0 + k, lim) : 0u;
-        store_lut8(lut + (row0 + (size_t)j) * (size_t)L + v0, e, n, lut_vec);
+        double x[8];
+        levels8(v0, x);
+        store_lut8(lut + (row0 + (size_t)j) * (size_t)L + v0,
+                   lut_eight(a[0], a[1], a[2], a[3], x, top2), n, lut_vec, true);
     }
 }
 

@@ -47,14 +47,14 @@ struct ApplyParams {
 // and headers, [bands][ceil(levels / 64)][detectors]; a block that does not
 // fit the form gets the header kDenseBad).
 hipError_t launch_dense_encode(const uint16_t* lut, int32_t bands, int32_t detectors,
-                               int32_t levels, uint64_t* planes, int16_t* heads,
+                               int32_t levels, uint64_t* planes, int16_t* heads, int xcds,
                                hipStream_t stream);
 
 // LUT build that also writes each row's dense encoding ([bands][blocks]
-// [detectors] planes and heads, as launch_dense_encode): one wave per row.
+// [detectors] planes and heads, as launch_dense_encode).
 hipError_t launch_lut_build_ws(const double* coeffs, int64_t rows, int32_t detectors,
                                int32_t levels, uint16_t* lut, uint64_t* planes, int16_t* heads,
-                               hipStream_t stream);
+                               int xcds, hipStream_t stream);
 
 // lut_build: one thread per 8 consecutive levels of one LUT row.
 hipError_t launch_lut_build(const double* coeffs, int64_t rows, int32_t levels, uint16_t* lut,

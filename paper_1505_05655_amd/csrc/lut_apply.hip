@@ -50,11 +50,11 @@ __global__ __launch_bounds__(MODE == kDense ? kDenseMaxThreads : 1024) void k_ap
     }
     int d0, weff;
     if (p.uneven) {
-        const int64_t units = p.detectors / p.vec;
+        const int64_t units = (p.detectors + p.vec - 1) / p.vec;
         const int u0 = (int)((int64_t)s * units / p.strips);
         const int u1 = (int)((int64_t)(s + 1) * units / p.strips);
         d0 = u0 * p.vec;
-        weff = (u1 - u0) * p.vec;
+        weff = min(u1 * p.vec, p.detectors) - d0;
     } else {
         const int W = 1 << p.log_strip;
         d0 = s * W;
@@ -96,7 +96,7 @@ void fill_row<RC_APPLY_VEC, RC_APPLY_UNROLL>(ApplyKernel* row) {
     static_assert(kPolicies == 6, "one fill_policy per cache policy");
 }
 
-#else  // the host side and the encoder
+#else  // the host side
 
 // Defined by the RC_APPLY_VEC / RC_APPLY_UNROLL compilations.
 template <> void fill_row<1, 4>(ApplyKernel* row);
@@ -109,29 +109,6 @@ template <> void fill_row<4, 4>(ApplyKernel* row);
 template <> void fill_row<4, 8>(ApplyKernel* row);
 template <> void fill_row<4, 16>(ApplyKernel* row);
 template <> void fill_row<8, 4>(ApplyKernel* row);
-
-// One thread per (row, 64-level block). Consecutive threads take the same
-// block of consecutive rows: their output words are consecutive (output
-// [band][block][detector]), and a wave's blocks are mostly of one kind
-// (interior, run of 0 or run of L-1), so it rarely runs every branch of
-// the encoder; each lane reads its block's 128 bytes as 16-byte loads.
-__global__ __launch_bounds__(256) void k_dense_encode(const uint16_t* __restrict__ lut,
-                                                      int64_t rows, int32_t detectors,
-                                                      int32_t levels, uint64_t* planes,
-                                                      int16_t* heads, int32_t vec16) {
-    const int NB = (levels + 63) >> 6;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= rows * NB) return;
-    const int64_t bands = rows / detectors;
-    const int64_t per_block = bands * detectors;  // threads per block index
-    const int blk = (int)(t / per_block);
-    const int64_t row = t - (int64_t)blk * per_block;
-    const int64_t b = row / detectors;
-    const int64_t d = row - b * detectors;
-    const size_t o = ((size_t)b * NB + (size_t)blk) * (size_t)detectors + (size_t)d;
-    dense_encode_row_block(lut + (size_t)row * (size_t)levels, levels, blk, vec16 != 0,
-                           planes + o, heads + o);
-}
 
 namespace {
 
@@ -196,18 +173,6 @@ hipError_t prepare_apply_kernels(size_t bytes, size_t* usable) {
             }
     *usable = dyn;
     return hipSuccess;
-}
-
-hipError_t launch_dense_encode(const uint16_t* lut, int32_t bands, int32_t detectors,
-                               int32_t levels, uint64_t* planes, int16_t* heads,
-                               hipStream_t stream) {
-    const int64_t rows = (int64_t)bands * detectors;
-    const int64_t items = rows * ((levels + 63) / 64);
-    if (items <= 0) return hipSuccess;
-    const int vec16 = (levels % 8 == 0 && ((uintptr_t)lut & 15u) == 0) ? 1 : 0;
-    hipLaunchKernelGGL(k_dense_encode, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, stream,
-                       lut, rows, detectors, levels, planes, heads, vec16);
-    return hipGetLastError();
 }
 
 hipError_t launch_apply(const ApplyParams& p, const rc_plan& plan, size_t lds_bytes,

@@ -64,7 +64,25 @@ void default_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t level
 // Checks a plan against a shape and device; fills `p` and `lds_bytes`.
 rc_status check_plan(const rc_plan& plan, int64_t lines, int32_t detectors, int32_t bands,
                      int32_t levels, int vmax, const DeviceInfo& di, ApplyParams* p,
-                     size_t* lds_bytes);
+                     size_t* lds_bytes, bool wide = false);
+
+// rc_correct with this plan, as if it were the library's choice (rc_correct_plan
+// runs a plan exactly as it is).
+rc_status correct_chosen(const uint16_t* dn, const uint16_t* lut, int64_t lines,
+                         int32_t detectors, int32_t bands, int32_t levels, uint16_t* out,
+                         const rc_plan& plan, hipStream_t stream);
+
+// Estimated best power-of-two strip and line chunks of the LDS paths.
+bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
+                const DeviceInfo& di, rc_plan* plan);
+
+// Rows whose alignment allows fewer than 8 pixels per lane (an odd detector
+// count, say): turns an LDS plan into the same tiles with 8 pixels per lane
+// through 16-byte accesses at 2-byte alignment, which a plan of the caller
+// cannot ask for (`wide` of check_plan). False, and *plan as it was, in place
+// (the last lane of a strip repeats pixels of the one before it) and for
+// strips too narrow for that.
+bool widen_plan(const uint16_t* dn, const uint16_t* out, int32_t detectors, rc_plan* plan);
 
 // Longest line chunk a tile may have (32-bit buffer offsets); < 1 if none fits.
 int64_t max_chunk_lines(int32_t detectors, int32_t threads, int32_t unroll);

@@ -395,7 +395,8 @@ rc_status rc_tune(const uint16_t* dn, const uint16_t* lut, int64_t lines, int32_
     rc_plan best_p = cands[0];
     rc_status st = RC_OK;
     for (const rc_plan& p : cands) {
-        if (rc_correct_plan(dn, lut, lines, detectors, bands, levels, out, &p, stream) != RC_OK)
+        // Timed as rc_correct will run it (see correct_chosen).
+        if (correct_chosen(dn, lut, lines, detectors, bands, levels, out, p, stream) != RC_OK)
             continue;  // not runnable for this shape/device
         float t = 0.f;
         if (cold) {
@@ -406,7 +407,7 @@ rc_status rc_tune(const uint16_t* dn, const uint16_t* lut, int64_t lines, int32_
                                         hipMemcpyDeviceToDevice, stream)) != hipSuccess)
                     break;
                 if ((e = hipEventRecord(e0, stream)) != hipSuccess) break;
-                rc_correct_plan(dn, lut, lines, detectors, bands, levels, out, &p, stream);
+                correct_chosen(dn, lut, lines, detectors, bands, levels, out, p, stream);
                 if ((e = hipEventRecord(e1, stream)) != hipSuccess) break;
                 if ((e = hipEventSynchronize(e1)) != hipSuccess) break;
                 if ((e = hipEventElapsedTime(&one, e0, e1)) != hipSuccess) break;
@@ -416,7 +417,7 @@ rc_status rc_tune(const uint16_t* dn, const uint16_t* lut, int64_t lines, int32_
         } else {
             if ((e = hipEventRecord(e0, stream)) != hipSuccess) break;
             for (int r = 0; r < reps; ++r)
-                rc_correct_plan(dn, lut, lines, detectors, bands, levels, out, &p, stream);
+                correct_chosen(dn, lut, lines, detectors, bands, levels, out, p, stream);
             if ((e = hipEventRecord(e1, stream)) != hipSuccess) break;
             if ((e = hipEventSynchronize(e1)) != hipSuccess) break;
             if ((e = hipEventElapsedTime(&t, e0, e1)) != hipSuccess) break;

@@ -60,3 +60,50 @@ def test_dense_tile_with_unencodable_blocks(kind, vec, threads, lines, chunk):
     torch.cuda.synchronize()
     out.check_pads()
     np.testing.assert_array_equal(out.host(), want)
+
+
+# Rows that the encoder has to tell apart: saturated at either end (run lengths around a lane's 8
+# and a block's 64 entries), constant, steps of 2 out of and into a saturated run, decreasing,
+# entries above levels - 1 and wrapping around 65535, and levels that end inside a lane, a block
+# and a pass of 512.
+def _odd_rows(L, rng):
+    v = np.arange(L)
+    rows = [np.clip(v - z, 0, L - 1) for z in (0, 1, 7, 8, 9, 63, 64, 65, 130)]
+    rows += [np.clip(v + z, 0, L - 1) for z in (1, 7, 8, 63, 64, 65, 200)]
+    rows += [np.full(L, c) for c in (0, 1, 5, L - 2, L - 1)]
+    rows += [np.where(v < 70, 0, np.minimum(v - 68, L - 1)), np.where(v < L - 70, v // 2, L - 1)]
+    rows += [np.clip((1.07 * v).astype(int) - 40, 0, L - 1), (0.93 * v).astype(int)]
+    rows += [L - 1 - v, np.where(v == 90, 3, v), np.where(v == L - 2, L - 5, v)]
+    rows += [v + 3 * (v > 100), np.minimum(v + 50, L + 20), (v + 65500) % 65536, v + L]
+    rows += [rng.integers(0, 65536, L), np.clip(2 * v - 31, 0, L - 1)]
+    return np.stack(rows).astype(np.uint16)
+
+
+@pytest.mark.parametrize("L", [2048, 2049, 2060, 2100, 2560, 3000, 4096, 8191])
+def test_encoder_on_odd_rows(L):
+    rng = np.random.default_rng(L)
+    lut = _odd_rows(L, rng)[None]
+    D = lut.shape[1]
+    # Every level of every row, and saturating DN.
+    dn = np.concatenate([np.arange(L + 3), rng.integers(0, 65536, 61)])[None, :, None]
+    dn = np.ascontiguousarray(np.broadcast_to(dn, (1, dn.shape[1], D))).astype(np.uint16)
+    want = oracle.get().correct(dn, lut)
+    N = dn.shape[1]
+    n = rc.rc_correct_ws_bytes(D, 1, L)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+    d_dn, d_lut = to_dev_u16(dn), to_dev_u16(lut)
+    for call in ("ws", "tile", "plain"):
+        out = Guarded((1, N, D))
+        if call == "ws":
+            rc.rc_correct_ws(d_dn, d_lut, N, D, 1, L, out.t, ws, n)
+        elif call == "tile":
+            plan = rc.Plan(path=rc.RC_PATH_DENSE, strip=64, vec=1, threads=256, unroll=8,
+                           chunk_lines=N, xcd_remap=1, nontemporal=0, strips=0, lane_map=0)
+            if 64 * ((L + 63) // 64) * 10 > 160 * 1024:
+                continue
+            rc.rc_correct_plan(d_dn, d_lut, N, D, 1, L, out.t, plan)
+        else:
+            rc.rc_correct(d_dn, d_lut, N, D, 1, L, out.t)
+        torch.cuda.synchronize()
+        out.check_pads()
+        np.testing.assert_array_equal(out.host(), want, err_msg=call)

@@ -1,0 +1,70 @@
+"""Rows whose alignment allows fewer than 8 pixels per lane (any detector count, 2-byte aligned
+images) through the library's own plans: 16-byte accesses at 2-byte alignment, the last lane of a
+strip repeating pixels of the one before it; in place they keep narrower lanes. Bit-exact against
+the oracle, no write outside the image."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+import paper_1505_05655_amd as rc  # noqa: E402
+import pins  # noqa: E402
+from gpu_util import Guarded, to_dev_f64, to_dev_u16, to_host_u16  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+# Detector counts around a lane (8), a strip (8 .. 512) and a wave's line segments; levels of the
+# raw, packed and dense strips; one row, less than a pass, several passes and chunks.
+DETECTORS = [1, 7, 8, 9, 15, 17, 31, 33, 63, 65, 100, 127, 129, 257, 511, 777, 1027]
+SHAPES = [(1, 2048), (300, 1024), (2500, 1024), (77, 4096), (3000, 2048),
+          (40, 300)]
+
+
+@pytest.mark.parametrize("D", DETECTORS)
+@pytest.mark.parametrize("off_in,off_out", [(0, 0), (1, 0), (3, 5)])
+def test_default_plans_on_any_row_length(D, off_in, off_out):
+    o = oracle.get()
+    for lines, L in SHAPES:
+        B = 2
+        coeffs, dn = pins.tiny_case(D * 31 + lines, B, lines, D, L)
+        coeffs[..., 1] = np.random.default_rng(D).uniform(0.9, 1.1, size=(B, D))
+        lut = o.lut_build(coeffs, L)
+        want = o.correct(dn, lut)
+        src = Guarded((B, lines, D), offset=off_in)
+        src.t.copy_(to_dev_u16(dn).view(B, lines, D))
+        d_lut = rc.lut_build(to_dev_f64(coeffs), L)
+        np.testing.assert_array_equal(to_host_u16(d_lut), lut)
+        calls = [lambda out: rc.rc_correct(src.t, d_lut, lines, D, B, L, out)]
+        n = rc.rc_correct_ws_bytes(D, B, L)
+        if n:
+            ws = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+            calls.append(lambda out: rc.rc_correct_ws(src.t, d_lut, lines, D, B, L, out, ws, n))
+        for call in calls:
+            out = Guarded((B, lines, D), offset=off_out)
+            call(out.t)
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(out.host(), want, err_msg=f"{lines} x {D}, L {L}")
+            out.check_pads()
+        # in place
+        rc.rc_correct(src.t, d_lut, lines, D, B, L, src.t)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(src.host(), want, err_msg=f"in place {lines} x {D}, L {L}")
+        src.check_pads()
+
+
+@pytest.mark.parametrize("D,off", [(333, 0), (1000, 1)])
+def test_the_reported_plan_runs_as_it_is(D, off):
+    """rc_plan_for's plan is one rc_correct_plan accepts, with the same result."""
+    lines, L, B = 700, 1024, 1
+    coeffs, dn = pins.tiny_case(D, B, lines, D, L)
+    o = oracle.get()
+    lut = o.lut_build(coeffs, L)
+    src = Guarded((B, lines, D), offset=off)
+    src.t.copy_(to_dev_u16(dn).view(B, lines, D))
+    out = Guarded((B, lines, D))
+    plan, _ = rc.rc_plan_for(lines, D, B, L, src.t, out.t)
+    rc.rc_correct_plan(src.t, to_dev_u16(lut), lines, D, B, L, out.t, plan)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(out.host(), o.correct(dn, lut))
+    out.check_pads()
