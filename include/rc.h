@@ -140,9 +140,9 @@ typedef struct {
  * The plan rc_correct uses for this shape (tuned if the plan cache has one,
  * else the default heuristic). Host only; enqueues nothing.
  * `source` (may be NULL) receives 1 for a tuned plan, 0 for the default.
- * Where the rows allow fewer than 8 pixels per lane and dn != out, rc_correct
- * runs this plan's LDS tiles with 8 pixels per lane all the same (16-byte
- * accesses at 2-byte alignment); rc_correct_plan runs a plan exactly as it is.
+ * Where the rows allow fewer than 8 pixels per lane, rc_correct may run this
+ * plan's LDS tiles with 8 pixels per lane all the same (16-byte accesses at
+ * 2-byte alignment); rc_correct_plan runs a plan exactly as it is.
  */
 rc_status rc_plan_for(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
                       const uint16_t* dn, const uint16_t* out, rc_plan* plan, int32_t* source);

@@ -493,7 +493,7 @@ void ws_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, in
 
 bool widen_plan(const uint16_t* dn, const uint16_t* out, int32_t detectors, rc_plan* plan) {
     rc_plan p = *plan;
-    if (p.path == RC_PATH_L2 || p.vec == 8 || dn == out || p.strip < 8 || detectors < 8)
+    if (p.path == RC_PATH_L2 || p.vec == 8 || p.strip < 8 || detectors < 8)
         return false;
     const int64_t pow2 = ((int64_t)detectors + p.strip - 1) / p.strip;
     if (p.strips > 0 || detectors - (pow2 - 1) * p.strip < 8) {
@@ -503,6 +503,8 @@ bool widen_plan(const uint16_t* dn, const uint16_t* out, int32_t detectors, rc_p
         if (strips > 1 && units / strips < 2) return false;
         p.strips = (int32_t)strips;
     }
+    // In place, the lanes that share pixels have to be in one wave.
+    if (dn == out && (p.lane_map != 0 || p.strip > 512)) return false;
     p.vec = 8;
     p.unroll = 4;
     *plan = p;

@@ -7,14 +7,20 @@
 #include <stdint.h>
 
 #include "rc.h"
+#include "runtime.h"
 
 namespace rc {
 
-constexpr int kBatchThreads = 1024;
-constexpr int kBatchUnroll = 4;
+constexpr int kBatchThreads = 512;
+// Threads of a workgroup that stream the image; all build the LUT strip.
+constexpr int kBatchStream = 256;
+// Lines per register set with 8 pixels per lane, and with 1 (bounds the
+// prefetch overshoot of either).
+constexpr int kBatchUnroll8 = 4;
+constexpr int kBatchUnroll = 8;
 constexpr size_t kBatchLds = 80 * 1024;
-// Resident workgroups per CU the batch launch aims for (2048 threads per CU).
-constexpr int kBatchPerCu = 2048 / kBatchThreads;
+// Resident workgroups per CU the batch launch aims for (two 80 KiB strips).
+constexpr int kBatchPerCu = 2;
 // Tile queues of the persistent kernel: one per XCD (workgroups are dispatched
 // to the XCDs round-robin, so workgroup i starts on queue i % kBatchQueues).
 constexpr int kBatchQueues = 8;
@@ -36,13 +42,16 @@ struct BatchReq {
     int32_t vec;
     int32_t mode;     // kRaw / kGlobal / kPacked / kDense
     int32_t lut_vec;  // LUT rows allow 16-byte loads/stores
-    int32_t fused;    // tiles build their LUT strip in LDS (kRaw / kPacked)
+    int32_t fused;    // tiles build their LUT strip in LDS (all modes but kGlobal)
     int32_t pad;
-    // kDense: the request's dense workspace, [bands][blocks][detectors]
-    // planes and headers, written by k_batch_encode before the tiles run.
-    uint64_t* planes;
-    int16_t* heads;
 };
+
+// First detector of strip s (the last strip of a request with 8 pixels per
+// lane has at least 8 detectors: it starts inside the one before it).
+inline int32_t strip_start(const BatchReq& q, int32_t s) {
+    const int32_t d0 = s << q.log_strip;
+    return q.vec == 8 && q.detectors - d0 < 8 ? q.detectors - 8 : d0;
+}
 
 struct BatchTile {
     int32_t req;
@@ -73,12 +82,16 @@ BatchQueues single_queue(int32_t n);
 // Sets the persistent kernel's dynamic LDS limit on the current device.
 hipError_t prepare_batch_kernel(size_t lds);
 
-// Fills q's strip shape and mode from a plain-path plan, fitted to the
-// persistent kernel's workgroup size and LDS budget. Dense plans keep the
-// dense mode only if allow_dense (the caller then provides the request's
-// dense workspace and runs k_batch_encode first); otherwise they become
-// packed.
-void fit_request_plan(const rc_plan& plan, int levels, size_t lds_cap, bool allow_dense,
-                      BatchReq* q);
+// Tile shape of a request without a batch entry: the plain path's tuned plan
+// if the cache has one, else dense strips for 2048 to 8192 levels (twice the
+// detectors of a packed strip in the same LDS), else pow2_plan's.
+void batch_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
+                const DeviceInfo& di, size_t lds_cap, rc_plan* plan);
+
+// Fills q's strip shape and mode from a plan, fitted to the persistent
+// kernel's workgroup size and LDS budget; 8 pixels per lane whatever the rows'
+// alignment, except for a request in place whose last strip would have to
+// overlap the one before it, and for fewer than 8 detectors.
+void fit_request_plan(const rc_plan& plan, int levels, size_t lds_cap, BatchReq* q);
 
 }  // namespace rc

@@ -1,11 +1,7 @@
 // Batched execution of many uneven correction requests (§I's LUT generation
 // and image correction, run for a whole queue of client scenes at once).
 //
-// Up to three kernels per run, captured once into a hipGraph and replayed:
-//  0. k_batch_encode: for the requests with dense tiles (levels <= 8192),
-//     one wave per LUT row evaluates the row from its coefficients, writes
-//     it to the request's LUT and its dense encoding to the batch's
-//     workspace, so the correction tiles only stage and stream.
+// Up to two kernels per run, captured once into a hipGraph and replayed:
 //  1. k_lut_build_batch: the LUT entries of the requests that are corrected
 //     from the global LUT (the L2 path, for level counts whose strips do not
 //     fit LDS); a thread finds its request by binary search over the prefix
@@ -13,24 +9,25 @@
 //  2. k_apply_batch: a persistent kernel (one workgroup per resident slot)
 //     whose workgroups pop tiles (request, band, strip, lines) from atomic
 //     queue heads, one queue per XCD: a workgroup drains its own XCD's queue,
-//     then helps with the others. For every other request a tile is fused: it evaluates its
-//     strip's LUT rows from the coefficients straight into LDS (the first
-//     line chunk of a strip also writes them to the request's LUT), then
-//     corrects its lines, so the LUT is never read back from memory and the
+//     then helps with the others. For every other request a tile is fused: it
+//     evaluates its strip's LUT rows from the coefficients straight into LDS
+//     (the first line chunk of a strip also writes them to the request's LUT),
+//     then corrects its lines, so the LUT is never read back from memory and the
 //     binary64 evaluation of one workgroup overlaps the streaming of others.
 //     The strips of one request line chunk stay together on one queue,
 //     groups are dealt longest first, so the tail of the batch is made of
 //     short tiles. The last workgroup to finish resets the counters, so a
 //     replay needs no memset node.
-// Strip width, LDS mode and pixels per lane per request come from the plan
-// the plain path would use for that request (tuned if the plan cache has
-// one), forced to the batch kernel's fixed workgroup size.
+// Strip width and LDS mode per request come from its batch entry of the plan
+// cache or from batch_plan, fitted to the kernel's workgroup size and LDS.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <climits>
+#include <cmath>
 #include <cstring>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "batch.h"
@@ -40,51 +37,6 @@
 #include "runtime.h"
 
 namespace rc {
-
-// Request r owns LUT rows [rprefix[r], rprefix[r + 1]) (band-major, detector
-// fastest); one wave per row.
-__global__ __launch_bounds__(256) void k_batch_encode(const BatchReq* __restrict__ reqs,
-                                                      const int64_t* __restrict__ rprefix,
-                                                      int32_t nreq, int64_t rows) {
-    const int64_t waves = (int64_t)gridDim.x * (blockDim.x >> 6);
-    const int64_t w0 = __builtin_amdgcn_readfirstlane(
-        (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6));
-    for (int64_t w = w0; w < rows; w += waves) {
-        int lo = 0, hi = nreq - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (rprefix[mid] <= w) lo = mid;
-            else hi = mid - 1;
-        }
-        const BatchReq& q = reqs[lo];
-        const int64_t row = w - rprefix[lo];
-        const int64_t b = row / q.detectors;
-        const int64_t d = row - b * q.detectors;
-        const int NB = (q.levels + 63) >> 6;
-        const double* a = q.coeffs + row * 4;
-        const size_t o = (size_t)b * (size_t)NB * (size_t)q.detectors + (size_t)d;
-        const int L = q.levels;
-        const bool vec = q.lut_vec != 0;
-        uint16_t* dst = q.lut + row * (int64_t)L;
-        uint64_t* planes = q.planes + o;
-        int16_t* heads = q.heads + o;
-        const size_t stride = (size_t)q.detectors;
-        const double a0 = a[0], a1 = a[1], a2 = a[2], a3 = a[3];
-        const uint32_t top2 = (uint32_t)(L - 1) * 0x10001u;
-        encode_rows<1>(
-            L,
-            [&](int v0, bool, u32x4 (&w)[1]) {
-                double x[8];
-                levels8(v0, x);
-                w[0] = lut_eight(a0, a1, a2, a3, x, top2);
-                if (v0 < L) store_lut8(dst + v0, w[0], L - v0, vec, true);
-            },
-            [&](int, int blk, uint64_t z, int16_t h) {
-                planes[(size_t)blk * stride] = z;
-                heads[(size_t)blk * stride] = h;
-            });
-    }
-}
 
 __global__ __launch_bounds__(256) void k_lut_build_batch(const BatchReq* __restrict__ reqs,
                                                          const int64_t* __restrict__ prefix,
@@ -118,42 +70,37 @@ __global__ __launch_bounds__(256) void k_lut_build_batch(const BatchReq* __restr
 template <int VEC>
 __device__ __forceinline__ void batch_tile_vec(const BatchReq& q, const BatchTile& tl,
                                                void* smem) {
+    constexpr int U = VEC == 8 ? kBatchUnroll8 : kBatchUnroll;
     const int W = 1 << q.log_strip;
     const int weff = min(W, q.detectors - tl.d0);
     if (q.fused) {
         const bool write_lut = tl.n0 == 0;
-        if (q.mode == kPacked) {
-            fused_tile<VEC, kBatchUnroll, kPacked>(q.coeffs, q.dn, q.lut, q.out, q.lines,
-                                                   q.detectors, q.levels, q.log_strip, tl.band,
-                                                   tl.d0, weff, tl.n0, tl.n1, write_lut, smem,
-                                                   q.lut_vec != 0);
-        } else {
-            fused_tile<VEC, kBatchUnroll, kRaw>(q.coeffs, q.dn, q.lut, q.out, q.lines,
-                                                q.detectors, q.levels, q.log_strip, tl.band,
-                                                tl.d0, weff, tl.n0, tl.n1, write_lut, smem,
-                                                q.lut_vec != 0);
-        }
-    } else if (q.mode == kDense) {
-        apply_tile<VEC, kBatchUnroll, 0, kDense, false>(q.dn, q.lut, q.out, q.lines, q.detectors,
-                                                        q.levels, q.log_strip, tl.band, tl.d0,
-                                                        weff, tl.n0, tl.n1, smem, q.lut_vec != 0,
-                                                        false, q.planes, q.heads);
+        auto run = [&](auto mode) {
+            fused_tile<VEC, U, decltype(mode)::value>(
+                q.coeffs, q.dn, q.lut, q.out, q.lines, q.detectors, q.levels, q.log_strip, tl.band,
+                tl.d0, weff, tl.n0, tl.n1, write_lut, smem, q.lut_vec != 0, kBatchStream);
+        };
+        if (q.mode == kPacked) run(std::integral_constant<int, kPacked>{});
+        else if (q.mode == kDense) run(std::integral_constant<int, kDense>{});
+        else run(std::integral_constant<int, kRaw>{});
     } else {
-        apply_tile<VEC, kBatchUnroll, false, kGlobal>(q.dn, q.lut, q.out, q.lines, q.detectors,
-                                                      q.levels, q.log_strip, tl.band, tl.d0,
-                                                      weff, tl.n0, tl.n1, smem, q.lut_vec != 0,
-                                                      false);
+        apply_tile<VEC, U, 0, kGlobal>(q.dn, q.lut, q.out, q.lines, q.detectors, q.levels,
+                                       q.log_strip, tl.band, tl.d0, weff, tl.n0, tl.n1, smem,
+                                       q.lut_vec != 0, false);
     }
 }
 
 // counters[q]: next tile of queue q; counters[kBatchQueues]: workgroups finished.
-// Two workgroups of kBatchThreads run per CU (8 waves per SIMD): the register
-// budget is set for that occupancy (64 VGPRs).
-__global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(8, 8)))
-void k_apply_batch(const BatchReq* __restrict__ reqs,
-                                                               const BatchTile* __restrict__ tiles,
-                                                               BatchQueues queues,
-                                                               unsigned int* counters) {
+// Two workgroups of kBatchThreads run per CU, 4 waves per SIMD: one streams
+// with 256 threads (16 bytes x 4 lines per lane and register set; with 1024
+// threads and 8 bytes the CU had 4 times the bytes in flight, and neighbouring
+// strips fetched the sectors they share again) while the other evaluates its
+// strip. 16 requests of 512 to 8192 lines and detectors, 1 to 4 bands, 10 and
+// 12 bit: 1.97 -> 1.85 ms from that, 8 pixels per lane on any row and dense
+// strips of 128 detectors for 4096 levels (packed: 64).
+__global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void k_apply_batch(const BatchReq* __restrict__ reqs, const BatchTile* __restrict__ tiles,
+                   BatchQueues queues, unsigned int* counters) {
     extern __shared__ __align__(16) unsigned char smem[];
     // The popped tile index is broadcast through the first word of the tile
     // LDS, which is dead between tiles (every tile ends with a barrier): no
@@ -175,8 +122,7 @@ void k_apply_batch(const BatchReq* __restrict__ reqs,
             if (t >= n) break;
             const BatchTile tl = tiles[lo + t];
             const BatchReq q = reqs[tl.req];
-            if (q.vec == 4) batch_tile_vec<4>(q, tl, smem);
-            else if (q.vec == 2) batch_tile_vec<2>(q, tl, smem);
+            if (q.vec == 8) batch_tile_vec<8>(q, tl, smem);
             else batch_tile_vec<1>(q, tl, smem);
         }
     }
@@ -215,18 +161,34 @@ hipError_t prepare_batch_kernel(size_t lds) {
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
-void fit_request_plan(const rc_plan& plan_in, int levels, size_t lds_cap, bool allow_dense,
-                      BatchReq* q) {
+void batch_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
+                const DeviceInfo& di, size_t lds_cap, rc_plan* plan) {
+    if (tuned_plan(lines, detectors, bands, levels, vmax, di, plan)) return;
+    pow2_plan(lines, detectors, bands, levels, vmax, di, plan);
+    if (levels < 2048 || levels > kDenseMaxLevels) return;
+    int W = 256;
+    while (W > 8 && (plan_lds_bytes(RC_PATH_DENSE, W, levels) > lds_cap || W / 2 >= detectors))
+        W >>= 1;
+    plan->path = RC_PATH_DENSE;
+    plan->strip = W;
+}
+
+void fit_request_plan(const rc_plan& plan_in, int levels, size_t lds_cap, BatchReq* q) {
     rc_plan p = plan_in;
-    if (p.vec > 4) p.vec = 4;  // the persistent kernel takes up to 4 pixels per lane
-    if (p.path == RC_PATH_DENSE && (!allow_dense || levels > kDenseMaxLevels))
-        p.path = RC_PATH_PACKED;
-    while (p.path != RC_PATH_L2 && plan_lds_bytes(p.path, p.strip, levels) > lds_cap &&
-           p.strip > p.vec)
+    if (p.path == RC_PATH_DENSE && levels > kDenseMaxLevels) p.path = RC_PATH_PACKED;
+    while (p.path != RC_PATH_L2 && plan_lds_bytes(p.path, p.strip, levels) > lds_cap && p.strip > 1)
         p.strip >>= 1;
     if (p.path != RC_PATH_L2 && plan_lds_bytes(p.path, p.strip, levels) > lds_cap)
         p.path = RC_PATH_L2;
-    if (p.strip / p.vec > kBatchThreads) p.strip = kBatchThreads * p.vec;
+    // In place, a line's overlapping lanes share a wave (strips of at most 512
+    // detectors), but overlapping strips would correct pixels twice.
+    const int rest = q->detectors % p.strip;
+    const bool in_place = q->dn == q->out;
+    p.vec = p.strip >= 8 && q->detectors >= 8 &&
+                    !(in_place && ((rest > 0 && rest < 8) || p.strip > 512))
+                ? 8
+                : 1;
+    while (p.strip / p.vec > kBatchStream) p.strip >>= 1;
     int lw = 0;
     while ((1 << (lw + 1)) <= p.strip) ++lw;
     q->log_strip = lw;
@@ -235,7 +197,7 @@ void fit_request_plan(const rc_plan& plan_in, int levels, size_t lds_cap, bool a
               : p.path == RC_PATH_PACKED ? kPacked
               : p.path == RC_PATH_DENSE  ? kDense
                                          : kGlobal;
-    q->fused = (q->mode == kRaw || q->mode == kPacked) ? 1 : 0;
+    q->fused = q->mode != kGlobal ? 1 : 0;
 }
 
 }  // namespace rc
@@ -253,9 +215,6 @@ struct rc_batch {
     BatchReq* d_reqs = nullptr;
     BatchTile* d_tiles = nullptr;
     int64_t* d_prefix = nullptr;
-    int64_t* d_rprefix = nullptr;   // LUT rows of the dense requests (k_batch_encode)
-    int64_t enc_rows = 0;
-    void* d_ws = nullptr;           // dense workspaces of those requests
     unsigned int* d_counters = nullptr;
     BatchQueues queues{};
     hipStream_t cap = nullptr;
@@ -276,8 +235,6 @@ void release(rc_batch* b) {
     if (b->d_reqs) (void)hipFree(b->d_reqs);
     if (b->d_tiles) (void)hipFree(b->d_tiles);
     if (b->d_prefix) (void)hipFree(b->d_prefix);
-    if (b->d_rprefix) (void)hipFree(b->d_rprefix);
-    if (b->d_ws) (void)hipFree(b->d_ws);
     if (b->d_counters) (void)hipFree(b->d_counters);
     delete b;
 }
@@ -339,14 +296,6 @@ rc_status validate_requests(const rc_request* reqs, int32_t n) {
 }
 
 hipError_t enqueue(const rc_batch* b, hipStream_t s) {
-    if (b->enc_rows > 0) {
-        const int64_t cap = (int64_t)std::max(1, b->cus) * 16;
-        const int64_t blocks = std::min<int64_t>((b->enc_rows + 3) / 4, cap);
-        hipLaunchKernelGGL(k_batch_encode, dim3((unsigned)blocks), dim3(256), 0, s, b->d_reqs,
-                           b->d_rprefix, b->nreq, b->enc_rows);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
     if (b->build_items > 0) {
         int64_t blocks = (b->build_items + 255) / 256;
         if (blocks > ((int64_t)1 << 20)) blocks = (int64_t)1 << 20;
@@ -366,6 +315,62 @@ hipError_t enqueue(const rc_batch* b, hipStream_t s) {
 
 namespace {
 
+// Cost of one detector's part of a tile, in image bytes: reading and writing
+// its lines, and evaluating its LUT row in a fused tile, which takes a
+// workgroup as long as 4 bytes per entry (1.1 entries and 1.1 pixels per ns
+// on the whole GPU), or reading it.
+int64_t detector_cost(const BatchReq& q, int64_t lines) {
+    return lines * 4 + (int64_t)q.levels * (q.fused ? 4 : 2);
+}
+
+// Line chunks of every request. A tile evaluates its strip whatever lines it
+// has, so fewer chunks are less work, but the last tiles to finish leave the
+// other workgroups idle: the batch takes the longest tile's time if every tile
+// has a workgroup, else about the workgroups' share of the work plus 0.6 of
+// the longest tile (fitted to a simulation of the queues with 4 to 16 requests
+// of 512 to 8192 lines and detectors). Tries bounds on the longest tile and
+// takes the best: 16 such requests 1.75 ms, with chunks of 8192 lines 1.85.
+std::vector<int64_t> line_chunks(const std::vector<BatchReq>& reqs, int slots) {
+    const size_t n = reqs.size();
+    std::vector<int64_t> best(n, 1), cur(n, 1);
+    double best_time = -1.0, longest0 = 0.0;
+    for (int step = 0; step < 8; ++step) {
+        static const double kBound[8] = {0.0, 0.7, 0.5, 0.35, 0.25, 0.18, 0.12, 0.08};
+        const double bound = step == 0 ? 1e300 : kBound[step] * longest0;
+        double total = 0.0, longest = 0.0, tiles = 0.0;
+        for (size_t i = 0; i < n; ++i) {
+            const BatchReq& q = reqs[i];
+            cur[i] = 1;
+            if (q.bands <= 0 || q.detectors <= 0) continue;
+            const int64_t cap = std::max<int64_t>(
+                1, std::min<int64_t>(8192, max_chunk_lines(q.detectors, kBatchThreads,
+                                                           kBatchUnroll)));
+            const int64_t kmin = std::max<int64_t>(1, (q.lines + cap - 1) / cap);
+            const double w = (double)std::min<int64_t>(1 << q.log_strip, q.detectors);
+            const double row = (double)detector_cost(q, 0);
+            // Lines that keep the tile within the bound, but not fewer than
+            // cost as much as the LUT strip.
+            const double fit = std::max(bound / w - row, row) / 4.0;
+            const int64_t k = fit >= (double)q.lines
+                                  ? 1
+                                  : (int64_t)std::ceil((double)q.lines / std::max(1.0, fit));
+            cur[i] = std::max(kmin, std::min<int64_t>(k, std::max<int64_t>(1, q.lines)));
+            const double lines = (double)((q.lines + cur[i] - 1) / cur[i]);
+            total += (double)q.bands * (double)q.detectors *
+                     ((double)q.lines * 4.0 + (double)cur[i] * row);
+            longest = std::max(longest, w * (lines * 4.0 + row));
+            tiles += (double)q.bands * std::ceil((double)q.detectors / w) * (double)cur[i];
+        }
+        if (step == 0) longest0 = longest;
+        const double t = tiles <= (double)slots ? longest : total / (double)slots + 0.6 * longest;
+        if (best_time < 0.0 || t < best_time) {
+            best_time = t;
+            best = cur;
+        }
+    }
+    return best;
+}
+
 // The batch of n requests; every request takes the tile shape *forced when
 // it is given (the tuner's candidates), else its batch entry of the plan
 // cache, else the plain path's plan fitted to the batch kernel.
@@ -384,11 +389,6 @@ rc_status batch_create(const rc_request* reqs, int32_t n, int32_t flags, const r
     std::vector<BatchReq> hreq;
     std::vector<BatchTile> htile;
     std::vector<int64_t> prefix(1, 0);
-    std::vector<int64_t> rprefix(1, 0);
-    // Dense workspace of request i: planes at ws_planes[i], headers at
-    // ws_heads[i] (bytes into the batch's workspace), each 256-byte aligned.
-    std::vector<size_t> ws_planes(n, 0), ws_heads(n, 0);
-    size_t ws_total = 0;
     int64_t total_px = 0, total_lut = 0, gather_lut = 0;
     int32_t ntuned = 0, nfused = 0;
     for (int32_t i = 0; i < n; ++i) {
@@ -415,61 +415,55 @@ rc_status batch_create(const rc_request* reqs, int32_t n, int32_t flags, const r
                 p = *forced;
             } else if (tuned_batch_shape(r.detectors, r.levels, vmax, *di, &p)) {
                 ++ntuned;
-            } else if (!tuned_plan(lines_p, r.detectors, r.bands, r.levels, vmax, *di, &p)) {
-                pow2_plan(lines_p, r.detectors, r.bands, r.levels, vmax, *di, &p);
+            } else {
+                batch_plan(lines_p, r.detectors, r.bands, r.levels, vmax, *di, lds_cap, &p);
             }
-            fit_request_plan(p, r.levels, lds_cap, true, &q);
+            fit_request_plan(p, r.levels, lds_cap, &q);
             if (q.mode == kGlobal) gather_lut += lut_n;  // read back by the gather
             else ++nfused;                                // never read back
-            if (q.mode == kDense) {
-                const size_t nbl = (size_t)rows * (size_t)((r.levels + 63) / 64);
-                ws_planes[i] = ws_total;
-                ws_total += (nbl * 8 + 255) & ~(size_t)255;
-                ws_heads[i] = ws_total;
-                ws_total += (nbl * 2 + 255) & ~(size_t)255;
-            }
-            const int lw = q.log_strip;
-            // One tile per (band, strip) and line chunk; strips of up to 8192
-            // lines are not split (re-staging the LUT strip per chunk would
-            // re-read it), longer ones are cut into chunks of at most 8192.
-            const int W = 1 << lw;
-            const int64_t cap = std::min<int64_t>(
-                8192, max_chunk_lines(r.detectors, kBatchThreads, kBatchUnroll));
-            if (cap < 1) return RC_EINVAL;  // lines too wide for 32-bit tile offsets
-            const int64_t ch = std::max<int64_t>(1, std::min<int64_t>(r.lines, cap));
-            for (int32_t b = 0; b < r.bands; ++b)
-                for (int32_t d0 = 0; d0 < r.detectors; d0 += W) {
-                    // A fused request with no lines still gets one tile per
-                    // strip, which only builds the LUT (the other modes'
-                    // LUTs come from the build kernels).
-                    const int64_t nend = (r.lines == 0 && q.fused) ? 1 : r.lines;
-                    for (int64_t n0 = 0; n0 < nend; n0 += ch) {
-                        BatchTile tl;
-                        tl.req = i;
-                        tl.band = b;
-                        tl.d0 = d0;
-                        tl.pad = 0;
-                        tl.n0 = n0;
-                        tl.n1 = std::min(r.lines, n0 + ch);
-                        htile.push_back(tl);
-                    }
-                }
+            if (max_chunk_lines(r.detectors, kBatchThreads, kBatchUnroll) < 1)
+                return RC_EINVAL;  // lines too wide for 32-bit tile offsets
         }
         hreq.push_back(q);
         const int64_t items =
             (rows > 0 && q.mode == kGlobal) ? rows * (int64_t)((r.levels + 7) / 8) : 0;
         prefix.push_back(prefix.back() + items);
-        rprefix.push_back(rprefix.back() + ((rows > 0 && q.mode == kDense) ? rows : 0));
         total_px += px;
         total_lut += lut_n;
     }
+    const int slots =
+        std::max(1, di->cus) *
+        (int)std::max<size_t>(1, std::min<size_t>(kBatchPerCu, di->lds_per_cu / lds_cap));
+    // One tile per (band, strip) and line chunk.
+    const std::vector<int64_t> chunks = line_chunks(hreq, slots);
+    for (int32_t i = 0; i < n; ++i) {
+        const BatchReq& q = hreq[i];
+        if (q.bands <= 0 || q.detectors <= 0) continue;
+        const int64_t ch = std::max<int64_t>(1, (q.lines + chunks[i] - 1) / chunks[i]);
+        const int32_t strips = (int32_t)(((int64_t)q.detectors + (1 << q.log_strip) - 1) >>
+                                         q.log_strip);
+        // A fused request with no lines still gets one tile per strip, which
+        // only builds the LUT (the other mode's LUTs come from the build
+        // kernel).
+        const int64_t nend = (q.lines == 0 && q.fused) ? 1 : q.lines;
+        for (int32_t b = 0; b < q.bands; ++b)
+            for (int32_t st = 0; st < strips; ++st)
+                for (int64_t n0 = 0; n0 < nend; n0 += ch) {
+                    BatchTile tl;
+                    tl.req = i;
+                    tl.band = b;
+                    tl.d0 = strip_start(q, st);
+                    tl.pad = 0;
+                    tl.n0 = n0;
+                    tl.n1 = std::min(q.lines, n0 + ch);
+                    htile.push_back(tl);
+                }
+    }
     if (htile.size() > (size_t)INT32_MAX) return RC_EINVAL;
-    // Cost of a tile: image bytes of the tile plus its LUT strip (a fused
-    // tile's binary64 evaluation counted like 6 bytes per entry).
     auto cost = [&](const BatchTile& t) {
         const BatchReq& q = hreq[t.req];
-        const int64_t w = std::min<int64_t>(1 << q.log_strip, q.detectors - t.d0);
-        return w * ((t.n1 - t.n0) * 4 + (int64_t)q.levels * (q.fused ? 6 : 2));
+        return std::min<int64_t>(1 << q.log_strip, q.detectors - t.d0) *
+               detector_cost(q, t.n1 - t.n0);
     };
     // Tiles of one (request, band, line chunk) are a group: its strips hold
     // neighbouring segments of the same lines, which share cache lines where a
@@ -533,12 +527,10 @@ rc_status batch_create(const rc_request* reqs, int32_t n, int32_t flags, const r
     bt->ntiles = (int32_t)htile.size();
     bt->queues = queues;
     bt->build_items = prefix.back();
-    bt->enc_rows = rprefix.back();
     bt->cus = di->cus;
     bt->lds = lds_cap;
     bt->use_graph = !(flags & RC_BATCH_NO_GRAPH);
-    bt->slots = std::max(1, di->cus) *
-                (int)std::max<size_t>(1, std::min<size_t>(kBatchPerCu, di->lds_per_cu / lds_cap));
+    bt->slots = slots;
     hipError_t e = hipSuccess;
     auto fail = [&](hipError_t err) {
         release(bt);
@@ -547,16 +539,6 @@ rc_status batch_create(const rc_request* reqs, int32_t n, int32_t flags, const r
     if (n > 0) {
         if ((e = hipMalloc(&bt->d_reqs, sizeof(BatchReq) * n)) != hipSuccess) return fail(e);
         if ((e = hipMalloc(&bt->d_prefix, sizeof(int64_t) * (n + 1))) != hipSuccess) return fail(e);
-        if ((e = hipMalloc(&bt->d_rprefix, sizeof(int64_t) * (n + 1))) != hipSuccess)
-            return fail(e);
-    }
-    if (ws_total > 0) {
-        if ((e = hipMalloc(&bt->d_ws, ws_total)) != hipSuccess) return fail(e);
-        for (int32_t i = 0; i < n; ++i) {
-            if (hreq[i].mode != kDense || !ws_heads[i]) continue;
-            hreq[i].planes = (uint64_t*)((char*)bt->d_ws + ws_planes[i]);
-            hreq[i].heads = (int16_t*)((char*)bt->d_ws + ws_heads[i]);
-        }
     }
     if (!htile.empty() &&
         (e = hipMalloc(&bt->d_tiles, sizeof(BatchTile) * htile.size())) != hipSuccess)
@@ -570,9 +552,6 @@ rc_status batch_create(const rc_request* reqs, int32_t n, int32_t flags, const r
                                 hipMemcpyHostToDevice, bt->cap)) != hipSuccess)
             return fail(e);
         if ((e = hipMemcpyAsync(bt->d_prefix, prefix.data(), sizeof(int64_t) * (n + 1),
-                                hipMemcpyHostToDevice, bt->cap)) != hipSuccess)
-            return fail(e);
-        if ((e = hipMemcpyAsync(bt->d_rprefix, rprefix.data(), sizeof(int64_t) * (n + 1),
                                 hipMemcpyHostToDevice, bt->cap)) != hipSuccess)
             return fail(e);
     }
@@ -612,18 +591,15 @@ rc_status batch_create(const rc_request* reqs, int32_t n, int32_t flags, const r
 // Candidate tile shapes of the batch kernel for requests with `levels`
 // levels, at most `dmax` detectors and vector width up to vmax: the LDS
 // paths at the widest strip that fits the batch's tile budget and narrower
-// ones, the L2 path at two widths, each with the widest and the next
-// pixels per lane.
+// ones, the L2 path at two widths.
 std::vector<rc_plan> batch_candidates(int32_t levels, int32_t dmax, int vmax, size_t lds_cap,
                                       int effort) {
     std::vector<rc_plan> out;
     int wcap = 8;
     while (wcap < dmax && wcap < 1024) wcap <<= 1;
-    std::vector<int> vecs;
-    for (int v = std::min(vmax, 4); v >= 1 && (int)vecs.size() < (effort ? 3 : 2); v >>= 1)
-        vecs.push_back(v);
-    auto add = [&](int path, int W, int vec) {
-        if (W < vec || W > wcap || W / vec > kBatchThreads) return;
+    auto add = [&](int path, int W) {
+        const int vec = std::min(vmax, 4);
+        if (W < vec || W > wcap) return;
         rc_plan p;
         std::memset(&p, 0, sizeof p);
         p.path = path;
@@ -644,11 +620,9 @@ std::vector<rc_plan> batch_candidates(int32_t levels, int32_t dmax, int vmax, si
                 break;
             }
         if (!w0) continue;
-        for (int k = 0; k < (effort ? 3 : 2); ++k)
-            for (int v : vecs) add(path, w0 >> k, v);
+        for (int k = 0; k < (effort ? 3 : 2); ++k) add(path, w0 >> k);
     }
-    for (int W : {64, 128})
-        for (int v : vecs) add(RC_PATH_L2, W, v);
+    for (int W : {64, 128}) add(RC_PATH_L2, W);
     return out;
 }
 
@@ -715,8 +689,7 @@ rc_status rc_batch_tune(const rc_request* reqs, int32_t n, int32_t effort, int32
             const rc_request& r0 = c.reqs.front();
             rc_plan h;
             const int64_t lines_p = std::max<int64_t>(r0.lines, 1);
-            if (!tuned_plan(lines_p, r0.detectors, r0.bands, r0.levels, c.vmax, *di, &h))
-                pow2_plan(lines_p, r0.detectors, r0.bands, r0.levels, c.vmax, *di, &h);
+            batch_plan(lines_p, r0.detectors, r0.bands, r0.levels, c.vmax, *di, lds_cap, &h);
             cands.push_back(h);
             for (const rc_plan& x : batch_candidates(c.levels, c.dmax, c.vmax, lds_cap, effort))
                 cands.push_back(x);

@@ -672,18 +672,16 @@ __device__ __forceinline__ int packed_any(int flag, u32x2* planes) {
 // a line of the strip and the workgroup walks floor(blockDim.x / q) lines at
 // a time. q = W / VEC (`dense` false: a wave covers whole line segments when
 // q divides 64, lanes past a narrower strip idle) or ceil(weff / VEC) (`dense`
-// true: no idle lanes inside a wave). If VEC does not divide weff (`dense`
-// only), the last lane of a line takes the strip's last VEC detectors, some of
-// which the lane before it takes too; both write the same values, so dn and
-// out must then not be the same buffer. Requirements (checked on the host): W
-// = 2^logW >= weff >= VEC, image pointers aligned to 2 bytes, W / VEC <=
-// blockDim.x, and the LDS size of the mode for W detectors. dn and out may be
-// the same buffer (in place) when VEC | weff: every pixel is read and then
-// written by the same lane, so they are deliberately not __restrict__.
-// LANE_ENCODE: the dense mode may encode its strip from the global LUT
-// (false: the caller always passes a pre-encoded strip, and the encoder is
-// not compiled in).
-template <int VEC, int UNROLL, int NT, int MODE, bool LANE_ENCODE = true>
+// true: no idle lanes inside a wave). If VEC does not divide weff, the last
+// lane of a line takes the strip's last VEC detectors, some of which the lane
+// before it takes too; both write the same values. Requirements (checked on
+// the host): W = 2^logW >= weff >= VEC, image pointers aligned to 2 bytes, W /
+// VEC <= blockDim.x, and the LDS size of the mode for W detectors. dn and out
+// may be the same buffer (in place) if VEC | weff (every pixel is read and
+// then written by the same lane) or if q divides 64 (`dense` false: a line's
+// lanes are in one wave, which has loaded a line whole before it stores any of
+// it), so they are deliberately not __restrict__.
+template <int VEC, int UNROLL, int NT, int MODE>
 __device__ __forceinline__ void apply_tile(const uint16_t* dn, const uint16_t* __restrict__ lut,
                                            uint16_t* out, int64_t N, int D, int L, int logW,
                                            int b, int d0, int weff, int64_t n0, int64_t n1,
@@ -816,7 +814,7 @@ __device__ __forceinline__ void apply_tile(const uint16_t* dn, const uint16_t* _
         }
         // Stage: a wave encodes kRows rows of the strip at a time (the loads of
         // a pass of all of them in flight together).
-        if (LANE_ENCODE && !pre_planes) {
+        if (!pre_planes) {
             constexpr int kRows = 4;
             const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), nwv = nt >> 6;
             for (int j0 = wv * kRows; j0 < weff; j0 += nwv * kRows) {
@@ -881,7 +879,7 @@ __device__ __forceinline__ void apply_tile(const uint16_t* dn, const uint16_t* _
             const uint16_t* lrow = strip_lut + (size_t)gj * Lz;
             if (grp >= ng || grow >= rpp || glane >= lanes || gpasses == 0) {
                 // nothing to stream
-            } else if (LANE_ENCODE && nbad <= (uint32_t)NB) {
+            } else if (nbad <= (uint32_t)NB) {
                 // Few: decode every pixel and keep the smallest header the
                 // lane read in each line; a lane that met such a block then
                 // takes those pixels from the LUT row. One branch per
@@ -1065,21 +1063,37 @@ __device__ __forceinline__ void apply_tile(const uint16_t* dn, const uint16_t* _
 // ---- fused LUT build + correction (batched requests) ------------------------------------
 
 // Computes the LUT rows of band b, detectors [d0, d0 + weff) from their
-// calibration coefficients straight into the LDS tile (raw or packed layout,
-// as the correction tile reads them) and, if `write_lut`, also into the
-// global LUT. Returns nonzero (the same on every thread) when a packed row
-// has a step outside 0..3; the LDS tile is then unusable.
+// calibration coefficients straight into the LDS tile (raw, packed or dense
+// layout, as the correction tile reads them) and, if `write_lut`, also into
+// the global LUT. Returns nonzero (the same on every thread) when a packed row
+// has a step outside 0..3, the LDS tile is then unusable, or the number of
+// blocks the dense form cannot hold.
 template <int VEC, int MODE>
-__device__ __forceinline__ int build_strip(const double* __restrict__ coeffs, uint16_t* lut, int D,
-                                           int L, int logW, int b, int d0, int weff,
-                                           bool write_lut, bool lut_vec, void* smem) {
+__device__ __forceinline__ uint32_t build_strip(const double* __restrict__ coeffs, uint16_t* lut,
+                                                int D, int L, int logW, int b, int d0, int weff,
+                                                bool write_lut, bool lut_vec, void* smem) {
     constexpr int LOGVEC = log_vec<VEC>();
     const int W = 1 << logW;
     const int tid = threadIdx.x, nt = blockDim.x;
     const int logq = logW - LOGVEC;
     const uint32_t top2 = (uint32_t)(L - 1) * 0x00010001u;
     const size_t row0 = (size_t)b * (size_t)D + (size_t)d0;
-    int bad = 0;
+    // Coefficients of row j (the last row past the strip), loaded a row ahead.
+    struct Row {
+        double a[4];
+    };
+    auto load_row = [&](int j) {
+        const double* a = coeffs + (row0 + (size_t)min(j, weff - 1)) * 4;
+        return Row{{a[0], a[1], a[2], a[3]}};
+    };
+    // The LDS positions of row j: among the whole lanes, and in the last lane
+    // of a line, which takes the strip's last VEC detectors (see apply_tile).
+    const int lanes = (weff + VEC - 1) >> LOGVEC;
+    auto at_positions = [&](int j, auto put) {
+        const int k = j - (weff - VEC);
+        if ((j >> LOGVEC) < lanes - 1) put(((j & (VEC - 1)) << logq) + (j >> LOGVEC));
+        if (k >= 0) put((k << logq) + lanes - 1);
+    };
     if constexpr (MODE == kRaw) {
         // Item = (detector j fastest, 8-level chunk): consecutive lanes write
         // consecutive LDS entries.
@@ -1103,6 +1117,37 @@ __device__ __forceinline__ int build_strip(const double* __restrict__ coeffs, ui
             if (write_lut) store_lut8(lut + (row0 + (size_t)j) * (size_t)L + v0, w, n, lut_vec, true);
         }
         __syncthreads();
+        return 0;
+    } else if constexpr (MODE == kDense) {
+        // A wave evaluates and encodes one row at a time, 8 blocks of 64
+        // levels per pass.
+        const int NB = (L + 63) >> 6;
+        uint64_t* planes = (uint64_t*)smem;
+        int16_t* heads = (int16_t*)((unsigned char*)smem + ((size_t)NB << (logW + 3)));
+        const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), nwv = nt >> 6;
+        int bad = 0;
+        Row next = load_row(wv);
+        for (int j = wv; j < weff; j += nwv) {
+            const Row r = next;
+            next = load_row(j + nwv);
+            uint16_t* dst = lut + (row0 + (size_t)j) * (size_t)L;
+            encode_rows<1>(
+                L,
+                [&](int v0, bool, u32x4 (&w)[1]) {
+                    double x[8];
+                    levels8(v0, x);
+                    w[0] = lut_eight(r.a[0], r.a[1], r.a[2], r.a[3], x, top2);
+                    if (write_lut && v0 < L) store_lut8(dst + v0, w[0], L - v0, lut_vec, true);
+                },
+                [&](int, int blk, uint64_t z, int16_t h) {
+                    bad += (int)(h == kDenseBad);
+                    at_positions(j, [&](int p) {
+                        planes[(blk << logW) + p] = z;
+                        heads[(blk << logW) + p] = h;
+                    });
+                });
+        }
+        return dense_bad_blocks(bad, planes, heads);
     } else {
         // A wave evaluates one detector row at a time, 16 blocks of 32 levels
         // per pass: lane 4g + q computes levels 32 (16 r + g) + 8q .. + 7, so
@@ -1118,17 +1163,17 @@ __device__ __forceinline__ int build_strip(const double* __restrict__ coeffs, ui
         const int nwv = nt >> 6;
         const int rounds = (NB + 15) >> 4;
         uint32_t wrong = 0;
+        Row next = load_row(wv);
         for (int j = wv; j < weff; j += nwv) {
-            const double* a = coeffs + (row0 + (size_t)j) * 4;
-            const double a0 = a[0], a1 = a[1], a2 = a[2], a3 = a[3];
+            const Row cur = next;
+            next = load_row(j + nwv);
             uint16_t* dst = lut + (row0 + (size_t)j) * (size_t)L;
-            const int p = ((j & (VEC - 1)) << logq) + (j >> LOGVEC);
             for (int r = 0; r < rounds; ++r) {
                 const int blk = (r << 4) + g;
                 const int v0 = (blk << 5) + (q << 3);
                 double x[8];
                 levels8(v0, x);
-                const u32x4 w = lut_eight(a0, a1, a2, a3, x, top2);
+                const u32x4 w = lut_eight(cur.a[0], cur.a[1], cur.a[2], cur.a[3], x, top2);
                 if (write_lut && v0 < L) store_lut8(dst + v0, w, L - v0, lut_vec, true);
                 // Step i of a block (bit i of the planes) is entry i+1 minus
                 // entry i; a step that leaves the block or the row is 0.
@@ -1153,18 +1198,15 @@ __device__ __forceinline__ int build_strip(const double* __restrict__ coeffs, ui
                               (q < 3 && v0 + 8 < L && (nx & 0xffffu) < (w.w >> 16))) ? 4u : 0u;
                 const uint32_t lo = quad_plane(d[0], d[1], d[2], d[3], 0, q);
                 const uint32_t hi = quad_plane(d[0], d[1], d[2], d[3], 1, q);
-                if (q == 0 && blk < NB) {
-                    u32x2 pl;
-                    pl.x = lo;
-                    pl.y = hi;
-                    planes[blk * W + p] = pl;
-                    bases[blk * W + p] = (uint16_t)w.x;
-                }
+                if (q == 0 && blk < NB)
+                    at_positions(j, [&](int p) {
+                        planes[blk * W + p] = u32x2{lo, hi};
+                        bases[blk * W + p] = (uint16_t)w.x;
+                    });
             }
         }
-        bad = packed_any((wrong & 0xFFFCFFFCu) != 0 ? 1 : 0, planes);
+        return (uint32_t)packed_any((wrong & 0xFFFCFFFCu) != 0 ? 1 : 0, planes);
     }
-    return bad;
 }
 
 // Writes the strip's LUT rows to global memory (second pass of a packed
@@ -1196,22 +1238,27 @@ __device__ __forceinline__ uint32_t g_glb_l2(__amdgpu_buffer_rsrc_t r, uint32_t 
 }
 
 // One fused tile of a batched request: build the strip's LUT in LDS from the
-// coefficients (writing it to the global LUT too when write_lut), then
-// correct lines [n0, n1) exactly as apply_tile does.
+// coefficients with every thread (writing it to the global LUT too when
+// write_lut), then correct lines [n0, n1) as apply_tile does, with the first
+// nst threads: as many bytes in flight as the plain tiles keep. Another
+// workgroup of the CU builds meanwhile.
 template <int VEC, int UNROLL, int MODE>
 __device__ __forceinline__ void fused_tile(const double* __restrict__ coeffs, const uint16_t* dn,
                                            uint16_t* lut, uint16_t* out, int64_t N, int D, int L,
                                            int logW, int b, int d0, int weff, int64_t n0,
-                                           int64_t n1, bool write_lut, void* smem, bool lut_vec) {
+                                           int64_t n1, bool write_lut, void* smem, bool lut_vec,
+                                           int nst) {
     constexpr int LOGVEC = log_vec<VEC>();
-    const int bad = build_strip<VEC, MODE>(coeffs, lut, D, L, logW, b, d0, weff, write_lut,
-                                           lut_vec, smem);
+    const uint32_t bad = build_strip<VEC, MODE>(coeffs, lut, D, L, logW, b, d0, weff, write_lut,
+                                                lut_vec, smem);
     if (n1 > n0) {
         const int tid = threadIdx.x;
         const int logq = logW - LOGVEC;
         const int lane = tid & ((1 << logq) - 1);
-        const int rpp = blockDim.x >> logq;
-        const int j = lane * VEC;
+        const int lanes = (weff + VEC - 1) >> LOGVEC;
+        const int rpp = nst >> logq;
+        const int j = min(lane << LOGVEC, weff - VEC);
+        const bool streams = tid < nst && lane < lanes;
         const uint32_t top = (uint32_t)(L - 1);
         const size_t tile0 = ((size_t)b * (size_t)N + (size_t)n0) * (size_t)D + (size_t)d0;
         const uint32_t span = (uint32_t)((((size_t)(n1 - n0) - 1) * (size_t)D + (size_t)weff) * 2);
@@ -1220,37 +1267,55 @@ __device__ __forceinline__ void fused_tile(const double* __restrict__ coeffs, co
         const uint32_t vo = (uint32_t)(((size_t)(tid >> logq) * (size_t)D + (size_t)j) * 2);
         const uint32_t line_stride = (uint32_t)rpp * (uint32_t)D * 2u;
         const int passes = (int)((n1 - n0 + (int64_t)rpp * UNROLL - 1) / ((int64_t)rpp * UNROLL));
-        if constexpr (MODE == kRaw) {
+        if (MODE != kRaw && bad) {
+            // Some levels read the LUT rows in memory: they have to be there.
+            if (!write_lut) write_strip(coeffs, lut, D, L, b, d0, weff, lut_vec);
+            __threadfence();
+            __syncthreads();
+        }
+        const __amdgpu_buffer_rsrc_t rl = make_rsrc(
+            lut + ((size_t)b * (size_t)D + (size_t)d0) * (size_t)L, (uint32_t)((size_t)weff * L * 2));
+        if (!streams) {
+            // nothing to stream
+        } else if constexpr (MODE == kRaw) {
             const uint16_t* tile = (const uint16_t*)smem;
-            if (j < weff) {
+            stream_lines<VEC, UNROLL, 0>(
+                rin, rout, vo, line_stride, passes,
+                [&](int k, uint32_t d) { return g_raw(tile, d, top, logW, j + k); });
+        } else if constexpr (MODE == kDense) {
+            const uint32_t hb = (uint32_t)((L + 63) >> 6) << (logW + 3);
+            if (!bad) {
                 stream_lines<VEC, UNROLL, 0>(
-                    rin, rout, vo, line_stride, passes,
-                    [&](int k, uint32_t d) { return g_raw(tile, d, top, logW, j + k); });
+                    rin, rout, vo, line_stride, passes, [&](int k, uint32_t d) {
+                        const uint32_t p = (uint32_t)((k << logq) + lane);
+                        return g_dense(d, top, logW, p * 8u, hb + p * 2u);
+                    });
+            } else {
+                stream_lines<VEC, UNROLL, 0>(
+                    rin, rout, vo, line_stride, passes, [&](int k, uint32_t d) {
+                        const uint32_t p = (uint32_t)((k << logq) + lane);
+                        const uint32_t v = d < top ? d : top;
+                        int h = 0;
+                        const uint32_t e = g_dense_min(d, top, logW, p * 8u, hb + p * 2u, h);
+                        return h == (int)kDenseBad
+                                   ? g_glb_l2(rl, (uint32_t)((j + k) * L * 2), v, top)
+                                   : e;
+                    });
             }
         } else {
             const int NB = (L + 31) >> 5;
             const u32x2* planes = (const u32x2*)smem;
             const uint16_t* bases = (const uint16_t*)(planes + (size_t)NB * (1 << logW));
             if (!bad) {
-                if (j < weff) {
-                    stream_lines<VEC, UNROLL, 0>(
-                        rin, rout, vo, line_stride, passes, [&](int k, uint32_t d) {
-                            return g_packed(planes, bases, d, top, logW, (k << logq) + lane);
-                        });
-                }
+                stream_lines<VEC, UNROLL, 0>(
+                    rin, rout, vo, line_stride, passes, [&](int k, uint32_t d) {
+                        return g_packed(planes, bases, d, top, logW, (k << logq) + lane);
+                    });
             } else {
-                if (!write_lut) write_strip(coeffs, lut, D, L, b, d0, weff, lut_vec);
-                __threadfence();
-                __syncthreads();
-                const size_t row0 = (size_t)b * (size_t)D + (size_t)d0;
-                const __amdgpu_buffer_rsrc_t rl =
-                    make_rsrc(lut + row0 * (size_t)L, (uint32_t)((size_t)weff * L * 2));
-                if (j < weff) {
-                    stream_lines<VEC, UNROLL, 0>(
-                        rin, rout, vo, line_stride, passes, [&](int k, uint32_t d) {
-                            return g_glb_l2(rl, (uint32_t)((j + k) * L * 2), d, top);
-                        });
-                }
+                stream_lines<VEC, UNROLL, 0>(
+                    rin, rout, vo, line_stride, passes, [&](int k, uint32_t d) {
+                        return g_glb_l2(rl, (uint32_t)((j + k) * L * 2), d, top);
+                    });
             }
         }
     }

@@ -79,9 +79,9 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
 // Rows whose alignment allows fewer than 8 pixels per lane (an odd detector
 // count, say): turns an LDS plan into the same tiles with 8 pixels per lane
 // through 16-byte accesses at 2-byte alignment, which a plan of the caller
-// cannot ask for (`wide` of check_plan). False, and *plan as it was, in place
-// (the last lane of a strip repeats pixels of the one before it) and for
-// strips too narrow for that.
+// cannot ask for (`wide` of check_plan). False, and *plan as it was, for
+// strips too narrow for that and, in place, where the last lane of a line,
+// which repeats pixels of the one before it, may be in another wave.
 bool widen_plan(const uint16_t* dn, const uint16_t* out, int32_t detectors, rc_plan* plan);
 
 // Longest line chunk a tile may have (32-bit buffer offsets); < 1 if none fits.

@@ -287,9 +287,8 @@ hipError_t admit(rc_server* s, const std::shared_ptr<Job>& jp) {
         const int vmax = j.pixels > 0 ? max_vec(q.dn, q.out, h.detectors) : 1;
         const int64_t lines_p = std::max<int64_t>(h.lines, 1);
         rc_plan p;
-        if (!tuned_plan(lines_p, h.detectors, h.bands, h.levels, vmax, *s->di, &p))
-            pow2_plan(lines_p, h.detectors, h.bands, h.levels, vmax, *s->di, &p);
-        fit_request_plan(p, h.levels, s->lds, false, &q);
+        batch_plan(lines_p, h.detectors, h.bands, h.levels, vmax, *s->di, s->lds, &p);
+        fit_request_plan(p, h.levels, s->lds, &q);
     }
     // Pieces: per band, runs of lines of about piece_pixels pixels.
     const int64_t cap = std::min<int64_t>(
@@ -429,13 +428,12 @@ bool launch_quantum(rc_server* s, hipError_t* err) {
         } else {
             ri = it->second;
         }
-        const int W = 1 << j->req.log_strip;
         const int take = std::min(per_piece, std::min(pc->ntiles - pc->next_tile, max_tiles - nt));
         for (int k = 0; k < take; ++k) {
             BatchTile& tl = sl.h_tiles[nt++];
             tl.req = ri;
             tl.band = pc->band;
-            tl.d0 = (pc->next_tile + k) * W;
+            tl.d0 = strip_start(j->req, pc->next_tile + k);
             tl.pad = 0;
             tl.n0 = pc->n0;
             tl.n1 = pc->n1;
