@@ -210,21 +210,28 @@ def lib():
 
 
 def _ptr(x):
-    if x is None:
-        return None
-    if isinstance(x, int):
-        return x
     if isinstance(x, torch.Tensor):
-        if x.numel() and not x.is_cuda:
+        n = x.numel()
+        if n and not x.is_cuda:
             raise ValueError("expected a device tensor")
         if not x.is_contiguous():
             raise ValueError("expected a contiguous tensor")
-        return x.data_ptr() if x.numel() else None
+        return x.data_ptr() if n else None
+    if x is None or isinstance(x, int):
+        return x
     raise TypeError(f"expected a tensor or an int pointer, got {type(x)}")
+
+
+# The current stream's handle without a torch.cuda.Stream object around it
+# (0.1 instead of 2.7 us, a third of what a call cost), where this torch has
+# the accessor its own generated code uses.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(s):
     if s is None:
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(s, int):
         return s

@@ -230,6 +230,23 @@ bool balanced_tiling(int64_t lines, int32_t detectors, int32_t bands, int vec, i
 // 4 x 12000 x 12000 466 against 460 (a tuned plan). False if nothing fits.
 bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
                 const DeviceInfo& di, rc_plan* plan) {
+    // A program's next scene mostly has the last one's shape: the plan, which
+    // depends on nothing else, is kept per thread (the search takes 1.5 us).
+    struct Last {
+        const DeviceInfo* di = nullptr;
+        int64_t lines = 0;
+        int32_t detectors = 0, bands = 0, levels = 0;
+        int vmax = 0;
+        bool found = false;
+        rc_plan plan{};
+    };
+    static thread_local Last last;
+    if (last.di == &di && last.lines == lines && last.detectors == detectors &&
+        last.bands == bands && last.levels == levels && last.vmax == vmax) {
+        if (last.found) *plan = last.plan;
+        return last.found;
+    }
+    last.di = nullptr;
     const int64_t cus = std::max(1, di.cus);
     const size_t budget = std::min(di.lds ? di.lds : (size_t)65536,
                                    di.lds_per_cu ? di.lds_per_cu : (size_t)65536);
@@ -286,6 +303,7 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
     // sectors and lose up to 25 % where neighbouring tiles complete them.
     p.nontemporal = detectors % 32 == 0 && p.strip >= 32 ? 2 : 0;
     if (found) *plan = p;
+    last = Last{&di, lines, detectors, bands, levels, vmax, found, p};
     return found;
 }
 
