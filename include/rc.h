@@ -127,7 +127,8 @@ typedef struct {
                             4 sc1 loads + non-temporal stores, 5 sc0 loads */
     int32_t strips;      /* strips per band. 0: ceil(detectors / W) strips of W detectors (the
                             last one narrower). > 0: exactly this many strips of nearly equal
-                            width (multiples of vec, each at most W), so that the tile count
+                            width (multiples of vec, or of 64 where detectors is a multiple of
+                            32 and W allows it; each at most W), so that the tile count
                             bands * strips * line chunks can match the device's resident
                             workgroups: every workgroup then streams the same share of the
                             image and stages its LUT strip once */

@@ -206,8 +206,8 @@ bool balanced_tiling(int64_t lines, int32_t detectors, int32_t bands, int vec, i
     return true;
 }
 
-// The power-of-two strip W (raw or packed) and line chunk count k of least
-// estimated time, 256 threads with 16 bytes x 4 lines per lane and register
+// The strip width W (raw or packed) and line chunk count k of least estimated
+// time, 256 threads with 16 bytes x 4 lines per lane and register
 // set (half or twice the bytes in flight per CU were slower by 20 % and 10 %
 // on every large scene). The estimate, in us, of a launch of B x ceil(D / W)
 // x k tiles:
@@ -226,8 +226,10 @@ bool balanced_tiling(int64_t lines, int32_t detectors, int32_t bands, int vec, i
 // average, 1.13 at worst, and was at least as fast as the former default (W =
 // 256 or 64, about two rounds of 512-thread tiles but few line chunks) on all:
 // 1 x 30000 x 2000 at 4096 levels 69 against 163 us, 4 x 3000 x 1000 at 1024
-// 14 against 103, 1 x 512 x 512 8 against 34, 3 x 5400 x 4096 68 against 111,
-// 4 x 12000 x 12000 466 against 460 (a tuned plan). False if nothing fits.
+// 14 against 103, 1 x 512 x 512 8 against 34, 3 x 5400 x 4096 68 against 111.
+// Strips of 192 and other multiples of whole 128-byte lines came after that
+// fit: 4 x 12000 x 12000 428 against 466 with W = 256 (460 tuned). False if
+// nothing fits.
 bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
                 const DeviceInfo& di, rc_plan* plan) {
     // A program's next scene mostly has the last one's shape: the plan, which
@@ -257,16 +259,22 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
     double best = 0.0;
     bool found = false;
     const double image = 4.0 * (double)bands * (double)lines * (double)detectors;
-    for (int W = 8; W <= 512; W <<= 1) {
+    // Powers of two, and for rows that start on 64-byte sectors the other
+    // multiples of 64 (strips of whole 128-byte lines, see check_plan).
+    for (int width : {8, 16, 32, 64, 128, 192, 256, 320, 384, 448, 512}) {
+        int W = 8;
+        while (W < width) W <<= 1;
         if (W > 8 && W / 2 >= detectors) break;
+        const bool pow2 = width == W;
+        if (!pow2 && detectors % 32 != 0) continue;
         const int vec = std::min(std::min(vmax, 8), W);
         const int unroll = vec == 8 ? 4 : 8;
         const int64_t cap = max_chunk_lines(detectors, p.threads, unroll);
         if (cap < 1) return false;
         const int64_t kmin = std::max<int64_t>(1, (lines + cap - 1) / cap);
-        const int64_t strips = ((int64_t)detectors + W - 1) / W;
+        const int64_t strips = ((int64_t)detectors + width - 1) / width;
         const int64_t base = strips * bands;
-        const double w = std::min(W, detectors);
+        const double w = std::min(width, detectors);
         for (int path : {RC_PATH_LDS, RC_PATH_PACKED}) {
             if (path == RC_PATH_PACKED && levels < 512) continue;
             const size_t lds = plan_lds_bytes(path, W, levels);
@@ -276,7 +284,7 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
             for (int64_t k = kmin; k <= kmax; ++k) {
                 const double per_tile = (double)lines / (double)k;
                 // Lines a pass takes, and the share of the last one's that exist.
-                const double pass = (double)std::max(1, p.threads / std::max(1, W / vec)) * unroll;
+                const double pass = (double)std::max(1, p.threads / std::max(1, width / vec)) * unroll;
                 const double waste = std::min(1.5, std::ceil(per_tile / pass) * pass / per_tile);
                 const double eff = w / (w + 5.0 + 50.0 * std::min(1.0, per_tile / 20000.0));
                 const int64_t tiles = base * k;
@@ -293,6 +301,8 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
                 best = t;
                 p.path = path;
                 p.strip = W;
+                p.strips = pow2 ? 0 : (int32_t)strips;
+                p.lane_map = pow2 ? 0 : 1;
                 p.vec = vec;
                 p.unroll = unroll;
                 p.chunk_lines = (int32_t)std::min<int64_t>((lines + k - 1) / k, INT32_MAX);
@@ -413,7 +423,15 @@ rc_status check_plan(const rc_plan& plan, int64_t lines, int32_t detectors, int3
     p->log_strip = ilog2(plan.strip);
     p->strips = (int32_t)strips;
     p->uneven = plan.strips > 0 ? 1 : 0;
-    p->vec = plan.vec;
+    p->unit = plan.vec;
+    if (plan.strips > 0 && detectors % 32 == 0) {
+        // Rows that start on 64-byte sectors: strips of whole 128-byte lines,
+        // unless that makes the widest strip wider than W.
+        const int64_t lines128 = ((int64_t)detectors + 63) / 64;
+        if (lines128 >= plan.strips &&
+            64 * ((lines128 + plan.strips - 1) / plan.strips) <= plan.strip)
+            p->unit = 64;
+    }
     p->dense = plan.lane_map;
     p->chunks = (int32_t)chunks;
     p->chunk_lines = plan.chunk_lines;

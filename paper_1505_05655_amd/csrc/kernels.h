@@ -25,8 +25,9 @@ struct ApplyParams {
     int32_t log_strip;   // log2(W): LDS tile width, widest strip
     int32_t strips;      // strips per band: ceil(D / W), or the plan's count when uneven
     int32_t uneven;      // 1: strip s is detector units [s*U/strips, (s+1)*U/strips) with
-                         //    U = D / vec (units of vec detectors); 0: strip s is [s*W, s*W+W)
-    int32_t vec;         // pixels per lane (the unit of uneven strips)
+                         //    U = ceil(D / unit) (units of `unit` detectors, the last one
+                         //    maybe partial); 0: strip s is [s*W, s*W+W)
+    int32_t unit;        // detectors per unit: pixels per lane, or 64 (see check_plan)
     int32_t dense;       // lanes per strip line: 0 W / vec, 1 strip width / vec
     int32_t chunks;      // ceil(N / chunk_lines)
     int64_t chunk_lines;

@@ -50,11 +50,11 @@ __global__ __launch_bounds__(MODE == kDense ? kDenseMaxThreads : 1024) void k_ap
     }
     int d0, weff;
     if (p.uneven) {
-        const int64_t units = (p.detectors + p.vec - 1) / p.vec;
+        const int64_t units = (p.detectors + p.unit - 1) / p.unit;
         const int u0 = (int)((int64_t)s * units / p.strips);
         const int u1 = (int)((int64_t)(s + 1) * units / p.strips);
-        d0 = u0 * p.vec;
-        weff = min(u1 * p.vec, p.detectors) - d0;
+        d0 = u0 * p.unit;
+        weff = min(u1 * p.unit, p.detectors) - d0;
     } else {
         const int W = 1 << p.log_strip;
         d0 = s * W;
