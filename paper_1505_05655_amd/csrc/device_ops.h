@@ -443,9 +443,12 @@ __device__ __forceinline__ uint32_t pk_add(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, a) +
                                                 __builtin_bit_cast(u16x2, b)));
 }
+// (As an instruction: the compiler turns a minimum with 1 into a comparison
+// per half.)
 __device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a),
-                                                                  __builtin_bit_cast(u16x2, b)));
+    uint32_t r;
+    asm("v_pk_min_u16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
 }
 
 // The step bits x0 .. x3 of a lane (bit 0 of each half), as one byte.
@@ -568,16 +571,27 @@ __device__ __forceinline__ void encode_pass(const u32x4 w, int L, int blk, bool 
 // All blocks of R rows of L levels: fetch(r, v0, whole, w) gives every row's 8
 // entries from level v0 of pass r (words past the row are ignored; several
 // rows per pass keep several loads in flight), put(i, blk, plane, header)
-// takes row i's block from lane q = 0. Every lane of the wave must call it.
-template <int R, typename F, typename P>
+// takes row i's block from lane q = 0. AHEAD: a pass's entries are fetched
+// while the one before is encoded (for fetches that load). Every lane of the
+// wave must call it.
+template <int R, bool AHEAD, typename F, typename P>
 __device__ __forceinline__ void encode_rows(int L, F fetch, P put) {
     const int NB = (L + 63) >> 6;
     const int lane = (int)(threadIdx.x & 63);
-    for (int r = 0; r < ((NB + 7) >> 3); ++r) {
+    const int rounds = (NB + 7) >> 3;
+    u32x4 next[R];
+    if (AHEAD) fetch(lane << 3, 512 <= L, next);
+    for (int r = 0; r < rounds; ++r) {
         const int blk = (r << 3) + (lane >> 3);
         const bool whole = ((r + 1) << 9) <= L;
         u32x4 w[R];
-        fetch((r << 9) + (lane << 3), whole, w);
+        if (AHEAD) {
+#pragma unroll
+            for (int i = 0; i < R; ++i) w[i] = next[i];
+            if (r + 1 < rounds) fetch(((r + 1) << 9) + (lane << 3), ((r + 2) << 9) <= L, next);
+        } else {
+            fetch((r << 9) + (lane << 3), whole, w);
+        }
 #pragma unroll
         for (int i = 0; i < R; ++i) {
             uint64_t z;
@@ -818,7 +832,7 @@ __device__ __forceinline__ void apply_tile(const uint16_t* dn, const uint16_t* _
             constexpr int kRows = 4;
             const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), nwv = nt >> 6;
             for (int j0 = wv * kRows; j0 < weff; j0 += nwv * kRows) {
-                encode_rows<kRows>(
+                encode_rows<kRows, true>(
                     L,
                     [&](int v0, bool whole, u32x4 (&w)[kRows]) {
 #pragma unroll
@@ -1131,7 +1145,7 @@ __device__ __forceinline__ uint32_t build_strip(const double* __restrict__ coeff
             const Row r = next;
             next = load_row(j + nwv);
             uint16_t* dst = lut + (row0 + (size_t)j) * (size_t)L;
-            encode_rows<1>(
+            encode_rows<1, false>(
                 L,
                 [&](int v0, bool, u32x4 (&w)[1]) {
                     double x[8];

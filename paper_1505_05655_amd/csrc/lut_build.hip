@@ -112,7 +112,7 @@ __global__ __launch_bounds__(256) void k_lut_build_ws(const double* __restrict__
             const int64_t b = (g * R + i) / detectors;
             o[i] = (size_t)b * (size_t)NB * (size_t)detectors + (size_t)(g * R + i - b * detectors);
         }
-        encode_rows<R>(
+        encode_rows<R, false>(
             levels,
             [&](int v0, bool, u32x4 (&w)[R]) {
                 double x[8];
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(256) void k_dense_encode(const uint16_t* __restrict
             const int64_t b = (g * R + i) / detectors;
             o[i] = (size_t)b * (size_t)NB * (size_t)detectors + (size_t)(g * R + i - b * detectors);
         }
-        encode_rows<R>(
+        encode_rows<R, true>(
             levels,
             [&](int v0, bool whole, u32x4 (&w)[R]) {
 #pragma unroll
@@ -200,7 +200,7 @@ hipError_t launch_dense_encode(const uint16_t* lut, int32_t bands, int32_t detec
     const int64_t rows = (int64_t)bands * detectors;
     if (rows <= 0) return hipSuccess;
     const int vec = rows_vec(lut, levels) ? 1 : 0;
-    hipLaunchKernelGGL(k_dense_encode<4>, row_grid(rows, 4), dim3(256), 0, stream, lut, rows,
+    hipLaunchKernelGGL(k_dense_encode<1>, row_grid(rows, 1), dim3(256), 0, stream, lut, rows,
                        detectors, levels, vec, xcds, planes, heads);
     return hipGetLastError();
 }
