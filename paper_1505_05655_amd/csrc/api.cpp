@@ -206,32 +206,37 @@ bool balanced_tiling(int64_t lines, int32_t detectors, int32_t bands, int vec, i
     return true;
 }
 
-// The strip width W (raw or packed) and line chunk count k of least estimated
-// time, 256 threads with 16 bytes x 4 lines per lane and register
-// set (half or twice the bytes in flight per CU were slower by 20 % and 10 %
-// on every large scene). The estimate, in us, of a launch of B x ceil(D / W)
-// x k tiles:
-//  - staging a tile: W x L entries at 0.22 ns (packed) or 0.115 ns (raw);
-//  - streaming: the image at 6 TB/s (and 21 GB/s per tile) times W / (W + 5 +
-//    50 min(1, lines per tile / 20000)): neighbouring strips share the memory
-//    sectors at their ends, the more often twice the further their tiles have
-//    drifted apart;
+// The strip width w, LDS mode and line chunk count k of least estimated time,
+// 256 threads with 16 bytes x 4 lines per lane and register set (half or twice
+// the bytes in flight per CU were slower by 20 % and 10 % on every large
+// scene). The estimate, in us, of a launch of B x ceil(D / w) x k tiles:
+//  - staging a tile: w x L entries at a cost per mode;
+//  - streaming: the image at 6 TB/s (and per_tile at most) times w / (w + ends
+//    + drift min(1, lines per tile / 20000)): neighbouring strips share the
+//    memory sectors at their ends, the more often fetched twice the further
+//    their tiles have drifted apart (more so where the lanes of a line do not
+//    divide a wave);
 //  - one round of tiles (at most one per CU) stages, then streams; more tiles
 //    overlap the two, but their streams, far apart in the image, run at a
-//    third of the rate, which only a scene with fewer lines than levels makes
-//    up for.
-// Fitted to 32 scenes of 1-4 bands, 512-50000 lines, 512-12000 detectors and
-// 1024 or 4096 levels, timed with every W in {8 .. 512} and about 8 chunk
-// counts each: the plan chosen takes 1.03 times the best one's time on
-// average, 1.13 at worst, and was at least as fast as the former default (W =
-// 256 or 64, about two rounds of 512-thread tiles but few line chunks) on all:
-// 1 x 30000 x 2000 at 4096 levels 69 against 163 us, 4 x 3000 x 1000 at 1024
-// 14 against 103, 1 x 512 x 512 8 against 34, 3 x 5400 x 4096 68 against 111.
-// Strips of 192 and other multiples of whole 128-byte lines came after that
-// fit: 4 x 12000 x 12000 428 against 466 with W = 256 (460 tuned). False if
-// nothing fits.
+//    fraction of the rate, which only a scene with fewer lines than levels
+//    makes up for.
+// Rows that start on 64-byte sectors (D a multiple of 32) take power-of-two
+// strips and other multiples of 64 (whole 128-byte lines, see check_plan), any
+// other rows power-of-two strips and even divisions of the row into about 256
+// or 192 tiles: 16-byte lanes find no alignment there that they could keep.
+// Fitted to 32 scenes of the first kind and 15 of the second (1-4 bands,
+// 512-50000 lines, 512-12000 detectors, 1024 or 4096 levels), each timed with
+// all widths and about 8 chunk counts: the plan chosen takes 1.03 and 1.05
+// times the best one's time on average, and was at least as fast as the former
+// default (W = 256 or 64, about two rounds of 512-thread tiles but few line
+// chunks) on all. 1 x 30000 x 2000 at 4096 levels: 69 against 163 us; 4 x 3000
+// x 1000 at 1024: 14 against 103; 1 x 512 x 512: 8 against 34; 3 x 5400 x
+// 4096: 68 against 111; 4 x 12000 x 12000: 428 against 460 with a tuned plan;
+// even divisions against powers of two: 2 x 40000 x 4001 256 against 301, 2 x
+// 4700 x 5122 at 4096 79 against 86, 4 x 12000 x 11999 475 against 512. False
+// if nothing fits.
 bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
-                const DeviceInfo& di, rc_plan* plan) {
+                const DeviceInfo& di, rc_plan* plan, bool in_place) {
     // A program's next scene mostly has the last one's shape: the plan, which
     // depends on nothing else, is kept per thread (the search takes 1.5 us).
     struct Last {
@@ -239,12 +244,13 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
         int64_t lines = 0;
         int32_t detectors = 0, bands = 0, levels = 0;
         int vmax = 0;
-        bool found = false;
+        bool in_place = false, found = false;
         rc_plan plan{};
     };
     static thread_local Last last;
     if (last.di == &di && last.lines == lines && last.detectors == detectors &&
-        last.bands == bands && last.levels == levels && last.vmax == vmax) {
+        last.bands == bands && last.levels == levels && last.vmax == vmax &&
+        last.in_place == in_place) {
         if (last.found) *plan = last.plan;
         return last.found;
     }
@@ -256,64 +262,87 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
     std::memset(&p, 0, sizeof(p));
     p.threads = 256;
     p.xcd_remap = 1;
+    struct Model {
+        double raw, packed, dense, ends, drift, ragged, per_tile, overlapped;
+    };
+    static const Model kSectors = {1.15e-4, 2.2e-4, 1e9, 5.0, 50.0, 1.0, 21e3, 2e6};
+    static const Model kAnyRows = {6e-5, 1.4e-4, 1.2e-4, 2.0, 40.0, 1.6, 23.8e3, 1.2e6};
+    const bool sectors = detectors % 32 == 0;
+    const Model& m = sectors ? kSectors : kAnyRows;
     double best = 0.0;
     bool found = false;
     const double image = 4.0 * (double)bands * (double)lines * (double)detectors;
-    // Powers of two, and for rows that start on 64-byte sectors the other
-    // multiples of 64 (strips of whole 128-byte lines, see check_plan).
-    for (int width : {8, 16, 32, 64, 128, 192, 256, 320, 384, 448, 512}) {
+    const int64_t cap = max_chunk_lines(detectors, p.threads, 8);
+    if (cap < 1) return false;
+    const int64_t kmin = std::max<int64_t>(1, (lines + cap - 1) / cap);
+    // Strips of `width` detectors with k line chunks; even: S of nearly equal
+    // width instead of ceil(D / W) of W = width.
+    auto consider = [&](int width, int64_t strips, bool even, int64_t k) {
         int W = 8;
         while (W < width) W <<= 1;
-        if (W > 8 && W / 2 >= detectors) break;
-        const bool pow2 = width == W;
-        if (!pow2 && detectors % 32 != 0) continue;
-        const int vec = std::min(std::min(vmax, 8), W);
-        const int unroll = vec == 8 ? 4 : 8;
-        const int64_t cap = max_chunk_lines(detectors, p.threads, unroll);
-        if (cap < 1) return false;
-        const int64_t kmin = std::max<int64_t>(1, (lines + cap - 1) / cap);
-        const int64_t strips = ((int64_t)detectors + width - 1) / width;
-        const int64_t base = strips * bands;
         const double w = std::min(width, detectors);
-        for (int path : {RC_PATH_LDS, RC_PATH_PACKED}) {
+        const int64_t tiles = strips * bands * k;
+        const double per_tile = (double)lines / (double)k;
+        // Lines a pass takes, and the share of the last one's that exist.
+        const int lanes = std::max(1, width / 8);
+        const double pass = (double)std::max(1, p.threads / lanes) * 4.0;
+        const double waste = std::min(1.5, std::ceil(per_tile / pass) * pass / per_tile);
+        const double drift = m.drift * std::min(1.0, per_tile / 20000.0) *
+                             (even && 64 % lanes != 0 ? m.ragged : 1.0);
+        const double eff = w / (w + m.ends + drift);
+        const bool one_round = tiles <= cus;
+        const double rate = one_round ? std::min(6e6 * eff, m.per_tile * (double)tiles)
+                                      : m.overlapped * eff;  // bytes per us
+        const double stream = image * waste / rate;
+        const double rounds = (double)((tiles + cus - 1) / cus);
+        for (int path : {RC_PATH_LDS, RC_PATH_PACKED, RC_PATH_DENSE}) {
             if (path == RC_PATH_PACKED && levels < 512) continue;
+            if (path == RC_PATH_DENSE && (levels < 2048 || levels > kDenseMaxLevels || W > 256))
+                continue;
             const size_t lds = plan_lds_bytes(path, W, levels);
             if (lds > budget) continue;
-            const double stage = w * levels * (path == RC_PATH_LDS ? 1.15e-4 : 2.2e-4);
-            const int64_t kmax = std::max(kmin, std::min<int64_t>(cus / base, lines));
-            for (int64_t k = kmin; k <= kmax; ++k) {
-                const double per_tile = (double)lines / (double)k;
-                // Lines a pass takes, and the share of the last one's that exist.
-                const double pass = (double)std::max(1, p.threads / std::max(1, width / vec)) * unroll;
-                const double waste = std::min(1.5, std::ceil(per_tile / pass) * pass / per_tile);
-                const double eff = w / (w + 5.0 + 50.0 * std::min(1.0, per_tile / 20000.0));
-                const int64_t tiles = base * k;
-                const bool one_round = tiles <= cus;
-                const double rate = one_round ? std::min(6e6 * eff, 21e3 * (double)tiles)
-                                              : 2e6 * eff;  // bytes per us
-                const double stream = image * waste / rate;
-                const int conc = (int)std::max<size_t>(1, std::min<size_t>(8, budget / lds));
-                const double stages = stage * (double)((tiles + cus - 1) / cus);
-                const double t = one_round || conc == 1 ? stages + stream
-                                                        : std::max(stages, stream) + stage;
-                if (found && t >= best) continue;
-                found = true;
-                best = t;
-                p.path = path;
-                p.strip = W;
-                p.strips = pow2 ? 0 : (int32_t)strips;
-                p.lane_map = pow2 ? 0 : 1;
-                p.vec = vec;
-                p.unroll = unroll;
-                p.chunk_lines = (int32_t)std::min<int64_t>((lines + k - 1) / k, INT32_MAX);
-            }
+            const double stage = w * levels * (path == RC_PATH_LDS      ? m.raw
+                                               : path == RC_PATH_PACKED ? m.packed
+                                                                        : m.dense);
+            const double t = one_round || lds * 2 > budget
+                                 ? stage * rounds + stream
+                                 : std::max(stage * rounds, stream) + stage;
+            if (found && t >= best) continue;
+            found = true;
+            best = t;
+            p.path = path;
+            p.strip = W;
+            p.strips = even ? (int32_t)strips : 0;
+            p.lane_map = even ? 1 : 0;
+            p.vec = std::min(std::min(vmax, 8), W);
+            p.unroll = p.vec == 8 ? 4 : 8;
+            p.chunk_lines = (int32_t)std::min<int64_t>((lines + k - 1) / k, INT32_MAX);
         }
+    };
+    for (int width : {8, 16, 32, 64, 128, 192, 256, 320, 384, 448, 512}) {
+        const bool pow2 = (width & (width - 1)) == 0;
+        if (width > 8 && width / 2 >= detectors) break;
+        if (!pow2 && !sectors) continue;
+        const int64_t strips = ((int64_t)detectors + width - 1) / width;
+        const int64_t kmax = std::max(kmin, std::min<int64_t>(cus / (strips * bands), lines));
+        for (int64_t k = kmin; k <= kmax; ++k) consider(width, strips, !pow2, k);
     }
+    // In place, rows without 16-byte alignment keep 8 pixels per lane only on
+    // whole line segments per wave (widen_plan).
+    const bool divide = !sectors && !(in_place && vmax < 8);
+    const int64_t units = ((int64_t)detectors + 7) / 8;
+    for (int64_t target : {cus, cus * 3 / 4})
+        for (int64_t k = kmin; divide && k <= std::min<int64_t>(32, lines); ++k) {
+            const int64_t strips = std::min(units / 2, target / (bands * k));
+            if (strips < 1) break;
+            const int64_t width = 8 * ((units + strips - 1) / strips);
+            if (width <= 1024) consider((int)width, strips, true, k);
+        }
     // Non-temporal stores gain 2-8 % where every segment is whole 64-byte
     // sectors and lose up to 25 % where neighbouring tiles complete them.
     p.nontemporal = detectors % 32 == 0 && p.strip >= 32 ? 2 : 0;
     if (found) *plan = p;
-    last = Last{&di, lines, detectors, bands, levels, vmax, found, p};
+    last = Last{&di, lines, detectors, bands, levels, vmax, in_place, found, p};
     return found;
 }
 
@@ -321,7 +350,7 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
 // long LUT rows with many lines per tile, else strip_plan, else pow2_plan (the
 // L2 path, for LUT rows too long for LDS strips).
 void default_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
-                  const DeviceInfo& di, rc_plan* plan) {
+                  const DeviceInfo& di, rc_plan* plan, bool in_place) {
     rc_plan legacy;
     pow2_plan(lines, detectors, bands, levels, vmax, di, &legacy);
     const int64_t cus = std::max(1, di.cus);
@@ -356,7 +385,8 @@ void default_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t level
         *plan = p;
         return;
     }
-    if (legacy.path == RC_PATH_L2 || !strip_plan(lines, detectors, bands, levels, vmax, di, plan))
+    if (legacy.path == RC_PATH_L2 ||
+        !strip_plan(lines, detectors, bands, levels, vmax, di, plan, in_place))
         *plan = legacy;
 }
 
@@ -582,7 +612,7 @@ rc_status run_correct(const uint16_t* dn, const uint16_t* lut, int64_t lines, in
     } else if (use_ws) {
         ws_plan(lines, detectors, bands, levels, vmax, *di, &plan);
     } else if (!tuned_plan(lines, detectors, bands, levels, vmax, *di, &plan)) {
-        default_plan(lines, detectors, bands, levels, vmax, *di, &plan);
+        default_plan(lines, detectors, bands, levels, vmax, *di, &plan, dn == out);
     }
     if (use_ws && plan.path != RC_PATH_DENSE) return RC_EINVAL;
     ApplyParams p{};
@@ -742,7 +772,7 @@ rc_status rc_plan_for(int64_t lines, int32_t detectors, int32_t bands, int32_t l
     if (!di) return RC_EHIP;
     const int vmax = max_vec(dn, out, detectors, 8);
     const bool tuned = tuned_plan(lines, detectors, bands, levels, vmax, *di, plan);
-    if (!tuned) default_plan(lines, detectors, bands, levels, vmax, *di, plan);
+    if (!tuned) default_plan(lines, detectors, bands, levels, vmax, *di, plan, dn && dn == out);
     if (source) *source = tuned ? 1 : 0;
     return RC_OK;
 }

@@ -59,7 +59,7 @@ void ws_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, in
 
 // Default launch shape for a shape class (no tuning).
 void default_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
-                  const DeviceInfo& di, rc_plan* plan);
+                  const DeviceInfo& di, rc_plan* plan, bool in_place = false);
 
 // Checks a plan against a shape and device; fills `p` and `lds_bytes`.
 rc_status check_plan(const rc_plan& plan, int64_t lines, int32_t detectors, int32_t bands,
@@ -72,9 +72,9 @@ rc_status correct_chosen(const uint16_t* dn, const uint16_t* lut, int64_t lines,
                          int32_t detectors, int32_t bands, int32_t levels, uint16_t* out,
                          const rc_plan& plan, hipStream_t stream);
 
-// Estimated best power-of-two strip and line chunks of the LDS paths.
+// Estimated best strips and line chunks of the LDS paths.
 bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
-                const DeviceInfo& di, rc_plan* plan);
+                const DeviceInfo& di, rc_plan* plan, bool in_place);
 
 // Rows whose alignment allows fewer than 8 pixels per lane (an odd detector
 // count, say): turns an LDS plan into the same tiles with 8 pixels per lane

@@ -68,3 +68,31 @@ def test_the_reported_plan_runs_as_it_is(D, off):
     torch.cuda.synchronize()
     np.testing.assert_array_equal(out.host(), o.correct(dn, lut))
     out.check_pads()
+
+
+# Scenes whose plan divides the rows evenly (strips that are no power of two); 4-aligned and odd
+# detector counts, one and several line chunks, raw, packed and dense strips.
+@pytest.mark.parametrize("lines,D,L", [(2936, 9903, 1024), (8000, 3003, 1024), (3000, 12001, 4096),
+                                       (9000, 6004, 1024)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_evenly_divided_rows(lines, D, L, off):
+    B = 1
+    plan = rc.rc_plan_for(lines, D, B, L)[0].as_dict()
+    assert plan["strips"] > 0
+    coeffs, dn = pins.tiny_case(D, B, lines, D, L)
+    coeffs[..., 1] = np.random.default_rng(D).uniform(0.9, 1.1, size=(B, D))
+    o = oracle.get()
+    lut = o.lut_build(coeffs, L)
+    want = o.correct(dn, lut)
+    d_lut = rc.lut_build(to_dev_f64(coeffs), L)
+    src = Guarded((B, lines, D), offset=off)
+    src.t.copy_(to_dev_u16(dn).view(B, lines, D))
+    out = Guarded((B, lines, D), offset=2 * off)
+    rc.rc_correct(src.t, d_lut, lines, D, B, L, out.t)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(out.host(), want)
+    out.check_pads()
+    rc.rc_correct(src.t, d_lut, lines, D, B, L, src.t)  # in place
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(src.host(), want)
+    src.check_pads()
