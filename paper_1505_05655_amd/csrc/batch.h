@@ -82,12 +82,6 @@ BatchQueues single_queue(int32_t n);
 // Sets the persistent kernel's dynamic LDS limit on the current device.
 hipError_t prepare_batch_kernel(size_t lds);
 
-// Tile shape of a request without a batch entry: the plain path's tuned plan
-// if the cache has one, else dense strips for 2048 to 8192 levels (twice the
-// detectors of a packed strip in the same LDS), else pow2_plan's.
-void batch_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
-                const DeviceInfo& di, size_t lds_cap, rc_plan* plan);
-
 // Fills q's strip shape and mode from a plan, fitted to the persistent
 // kernel's workgroup size and LDS budget; 8 pixels per lane whatever the rows'
 // alignment, except for a request in place whose last strip would have to

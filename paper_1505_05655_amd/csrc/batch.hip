@@ -161,8 +161,11 @@ hipError_t prepare_batch_kernel(size_t lds) {
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
-void batch_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
-                const DeviceInfo& di, size_t lds_cap, rc_plan* plan) {
+// Tile shape of a request without a batch entry: the plain path's tuned plan
+// if the cache has one, else dense strips for 2048 to 8192 levels (twice the
+// detectors of a packed strip in the same LDS), else pow2_plan's.
+static void batch_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
+                       const DeviceInfo& di, size_t lds_cap, rc_plan* plan) {
     if (tuned_plan(lines, detectors, bands, levels, vmax, di, plan)) return;
     pow2_plan(lines, detectors, bands, levels, vmax, di, plan);
     if (levels < 2048 || levels > kDenseMaxLevels) return;
