@@ -9,8 +9,8 @@
 // lane owns 4 consecutive columns (one 8-byte load per row, three 8-byte
 // non-temporal stores per row, so a wave moves 512 contiguous bytes per
 // instruction) and walks down a band of rows with a three-row window in
-// registers: each row is loaded once (a band's two halo rows aside), two rows
-// ahead of the one being computed. The ring of three rows rotates by
+// registers: each row is loaded once (a band's two halo rows aside), three
+// rows ahead of the one being computed. The ring of three rows rotates by
 // renaming in a six-fold unrolled loop, so each row's colour parity is a
 // compile-time constant. The left and right neighbour columns come from the
 // adjacent lanes by DPP wave shifts; only the two lanes at a wave's edge load
@@ -138,21 +138,21 @@ __device__ __forceinline__ void run_band(const uint16_t* im, uint16_t* out, int 
     };
     // Ring slot of row x: (x - r0 + 1) mod 3; the row loop is unrolled six
     // times, so the ring rotates by renaming and every row's parity is a
-    // compile-time constant (r0 and the loop step are even). Two rows are in
-    // flight: L[(x - r0 - 1) mod 2] holds row x until it is unpacked.
+    // compile-time constant (r0 and the loop step are even). Three rows are in
+    // flight: L[(x - r0 - 1) mod 3] holds row x until it is unpacked.
     Row U[3];
     U[0] = unpack<EDGE>(fetch(r0 - 1), ln);
     U[1] = unpack<EDGE>(fetch(r0), ln);
-    Load L[2];
-    L[0] = fetch(r0 + 1);
-    L[1] = fetch(r0 + 2);  // r0 + 2 <= r1: bands have at least 2 rows
+    Load L[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) L[i] = fetch(min(r0 + 1 + i, r1));
     for (int base = r0; base < r1; base += 6) {
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
             const int r = base + k;
             if (r >= r1) break;
-            U[(k + 2) % 3] = unpack<EDGE>(L[k % 2], ln);  // row r + 1
-            if (r + 3 <= r1) L[k % 2] = fetch(r + 3);
+            U[(k + 2) % 3] = unpack<EDGE>(L[k % 3], ln);  // row r + 1
+            if (r + 4 <= r1) L[k % 3] = fetch(r + 4);
             finish_row((k & 1) == 0, U[k % 3], U[(k + 1) % 3], U[(k + 2) % 3],
                        out + (size_t)r * (size_t)W, plane, row_bytes, ln);
         }
@@ -195,17 +195,23 @@ __global__ __launch_bounds__(256) void k_demosaic(const uint16_t* __restrict__ r
 hipError_t launch_demosaic(const uint16_t* raw, int32_t images, int32_t H, int32_t W,
                            uint16_t* rgb, int cus, hipStream_t stream) {
     const int col_waves = (W / 4 + 63) / 64;
-    // Long bands (few, long row streams) unless the launch is small: about 8
-    // waves per CU over the launch, 12 when the whole launch is at most 64
-    // rows per such wave (one 2048 x 2048 image: 6-row bands); 4 to 128 rows.
-    // Measured on 16 images: 82.5 us at 128-row bands against 86 us at 32.
+    // Short bands, in the order of the rows: the waves that run at one time
+    // then read and write one stretch of each plane. Long bands, 8 to 12
+    // streams per CU all over the images, were slower: 16 x 2048 x 2048 99 us
+    // with 8 rows, 113 with 128 (5.4 against 4.7 TB/s); 13 x 1540 x 1608, whose
+    // rows do not start on 64-byte sectors, 55 us with 2 rows, 59 with 4, 74
+    // with 70. Rows that do gain nothing below 8 on large launches (4 x 2048 x
+    // 2048: 27.3 us with 8, 28.6 with 4); small ones take about 12 waves per CU
+    // (one such image in 6-row bands: 6.9 us, 7.5 with 4).
     if (cus <= 0) cus = 256;
     const int64_t col_total = (int64_t)images * col_waves;
-    const int64_t work = (int64_t)H * col_total;  // wave-rows
-    const int64_t target = (work <= (int64_t)64 * 8 * cus ? 12 : 8) * (int64_t)cus;
-    int64_t band = (work + target - 1) / target;
-    band = band < 4 ? 4 : (band > 128 ? 128 : band);
+    const bool sectors = W % 32 == 0 && ((uintptr_t)rgb & 63u) == 0;
+    const int64_t target = (int64_t)12 * cus;
+    int64_t band = ((int64_t)H * col_total + target - 1) / target;
+    band = !sectors ? 2 : band < 4 ? 4 : band > 8 ? 8 : band;
     band = (band + 1) & ~(int64_t)1;  // whole Bayer rows
+    // Well under 2^32 threads.
+    while (((int64_t)H + band - 1) / band * col_total >= (int64_t)1 << 25) band *= 2;
     const int bands = (int)(((int64_t)H + band - 1) / band);
     const int64_t waves = col_total * bands;
     const int64_t blocks = (waves + 3) / 4;

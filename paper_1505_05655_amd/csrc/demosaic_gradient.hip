@@ -20,21 +20,19 @@
 // Stage 1 reaches two rows and columns, stage 2 one more, so a lane keeps a
 // window of five raw rows (r-1 .. r+3) and three green rows (r-1 .. r+1) in
 // registers: per output row r it unpacks raw row r+3 (loaded during the
-// two previous rows), starts the load of row r+5, computes green row r+1 and
+// three previous rows), starts the load of row r+6, computes green row r+1 and
 // finishes row r. The window is a ring of six slots, and the row loop is
 // unrolled six times so the ring rotates by renaming, not by register moves,
 // and the colour parity of every row is a compile-time constant.
 // Neighbour columns come from the adjacent lanes by DPP wave shifts; the two
 // lanes at a wave's edge load the 4 columns beyond it instead, and the wave
 // computes the one green value beyond it that stage 2 needs (at column c0-1
-// in B rows for lane 0, c0+4 in R rows for lane 63). On large launches the
-// four waves of a workgroup hold adjacent columns and pass those values to
-// each other through LDS instead, so only the workgroup's outer waves compute
-// them. Virtual rows above and below the image are computed by the same code
-// from mirrored raw rows: the stencils are symmetric, so they equal the
-// mirrored green rows. Rows are read and written through buffer resources
-// that span one image row, which makes idle lanes and loads beyond the image
-// harmless (they read 0 and write nothing).
+// in B rows for lane 0, c0+4 in R rows for lane 63). Virtual rows above and
+// below the image are computed by the same code from mirrored raw rows: the
+// stencils are symmetric, so they equal the mirrored green rows. Rows are read
+// and written through buffer resources that span one image row, which makes
+// idle lanes and loads beyond the image harmless (they read 0 and write
+// nothing).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -81,9 +79,6 @@ struct Lane {
     uint32_t ex_shift;  // where column c0-3 (lane 0) or c0+6 (lane 63) sits in the edge dword
     bool at_start;      // c0 == 0: columns -1, -2 are mirrored
     bool at_end;        // c0 + 4 == W: columns W, W+1 are mirrored
-    int w;              // wave in the workgroup
-    bool xl, xr;        // left / right neighbour wave in the workgroup (same band)
-    uint32_t* xch;      // LDS exchange slots [row parity][wave]
 };
 
 // One raw row as a lane sees it: its 4 samples and the neighbour columns.
@@ -94,10 +89,13 @@ struct Raw {
     uint32_t exw;     // edge lanes: column c0-3 (lane 0) or c0+6 (lane 63) in bits ex_shift..+15
 };
 
-// One green row: the lane's 4 values and the two neighbour columns.
+// One green row: the lane's 4 values and the two neighbour columns, and the
+// colour differences X - G' at the columns that are not green.
 struct Green {
     uint32_t g[4];
     uint32_t gl, gr;  // columns c0-1 and c0+4
+    int d[4];         // only at non-green columns
+    int dl, dr;       // columns c0-1 (B rows) and c0+4 (R rows)
 };
 
 struct Load {
@@ -158,13 +156,13 @@ __device__ __forceinline__ uint32_t clamp16(int v) { return (uint32_t)min(max(v,
 
 // One of three estimates: e1 where g1 < g2, e2 where g2 < g1, their mean on a
 // tie; e1 and e2 are numerators over 2^s. Each rounds half up to
-// (2 e + 2^s) >> (s + 1), the tie to (e1 + e2 + 2^s) >> (s + 1): select
-// first, round once.
+// (2 e + 2^s) >> (s + 1), the tie to (e1 + e2 + 2^s) >> (s + 1): two selects
+// that differ on a tie, one three-operand sum, one rounding.
 template <int s>
 __device__ __forceinline__ uint32_t pick(uint32_t g1, uint32_t g2, int e1, int e2) {
-    const int one = g1 < g2 ? e1 : e2;
-    const int n = g1 == g2 ? e1 + e2 : 2 * one;
-    return clamp16((n + (1 << s)) >> (s + 1));
+    const int a = g1 < g2 ? e1 : e2;
+    const int b = g1 <= g2 ? e1 : e2;
+    return clamp16((a + b + (1 << s)) >> (s + 1));
 }
 
 // Stage 1 at one R or B pixel: own sample c, green neighbours gl/gr/gu/gd,
@@ -185,7 +183,7 @@ __device__ __forceinline__ uint32_t green_at(uint32_t c, uint32_t gl, uint32_t g
 // columns: from the adjacent lanes, mirrored at the image edges, or computed
 // by the wave's edge lanes. odd: a B row, non-green at odd columns (a
 // constant once the row loop is unrolled).
-template <bool EDGE, bool XCH>
+template <bool EDGE>
 __device__ __forceinline__ Green green_row(bool odd, const Raw& u2, const Raw& u1, const Raw& m,
                                            const Raw& d1, const Raw& d2, const Lane& ln) {
     Green G;
@@ -202,45 +200,32 @@ __device__ __forceinline__ Green green_row(bool odd, const Raw& u2, const Raw& u
     // The green value just beyond the wave: column c0-1 (odd, so non-green in
     // B rows) for lane 0, column c0+4 (even, non-green in R rows) for lane 63.
     // Every lane evaluates it; only the edge lanes keep the result.
-    // XCH: the four waves of the workgroup hold adjacent columns of one band,
-    // so a wave publishes the value its neighbour needs (lane 63's g[3] for
-    // B rows, lane 0's g[0] for R rows) in LDS, and only the waves at the
-    // workgroup's edges compute theirs. One barrier per green row, the same
-    // number in every wave (same band, no wave leaves early); a slot is
-    // rewritten two rows later, after the next row's barrier.
-    uint32_t extra;
-    bool have = false;
-    if (XCH) {
-        const int lane = threadIdx.x & 63;
-        uint32_t* slot = ln.xch + (odd ? 0 : 4);
-        if (odd) {
-            if (lane == 63) slot[ln.w] = G.g[3];
-        } else {
-            if (lane == 0) slot[ln.w] = G.g[0];
-        }
-        __syncthreads();
-        have = odd ? ln.xl : ln.xr;
-        if (have) extra = slot[odd ? ln.w - 1 : ln.w + 1];
-    }
-    if (!have) {
-        const uint32_t ex = ex_of(m, ln);
-        extra = odd ? green_at(m.l1, m.l2, m.v[0], u1.l1, d1.l1, ex, m.v[1], u2.l1, d2.l1)
-                    : green_at(m.r1, m.v[3], m.r2, u1.r1, d1.r1, m.v[2], ex, u2.r1, d2.r1);
-    }
+    const uint32_t ex = ex_of(m, ln);
+    const uint32_t extra =
+        odd ? green_at(m.l1, m.l2, m.v[0], u1.l1, d1.l1, ex, m.v[1], u2.l1, d2.l1)
+            : green_at(m.r1, m.v[3], m.r2, u1.r1, d1.r1, m.v[2], ex, u2.r1, d2.r1);
     G.gl = from_lower_lane(odd ? extra : m.l1, G.g[3]);
     G.gr = from_upper_lane(odd ? m.r1 : extra, G.g[0]);
     if (EDGE) {
         G.gl = ln.at_start ? G.g[1] : G.gl;  // column -1 reads 1
         G.gr = ln.at_end ? G.g[2] : G.gr;    // column W reads W-2
     }
+#pragma unroll
+    for (int j = odd ? 1 : 0; j < 4; j += 2) G.d[j] = (int)(m.v[j] - G.g[j]);
+    if (odd) G.dl = (int)(m.l1 - G.gl);
+    else G.dr = (int)(m.r1 - G.gr);
     return G;
 }
 
-// Stage 2 at a G pixel with green g0: a missing colour from the pair x1, x2
-// with greens g1, g2.
-__device__ __forceinline__ uint32_t pair_at(uint32_t x1, uint32_t x2, uint32_t g1, uint32_t g2,
-                                            uint32_t g0x2p1) {
-    return clamp16((int)(x1 + x2 + g0x2p1 - (g1 + g2)) >> 1);
+// Column t (-1 .. 4) of a row's colour differences, at a non-green column.
+__device__ __forceinline__ int dat(const Green& g, int t) {
+    return t < 0 ? g.dl : (t > 3 ? g.dr : g.d[t]);
+}
+
+// Stage 2 at a G pixel with green g0: a missing colour from the differences of
+// a pair.
+__device__ __forceinline__ uint32_t pair_at(int d1, int d2, uint32_t g0x2p1) {
+    return clamp16((d1 + d2 + (int)g0x2p1) >> 1);
 }
 
 // Stage 2 at an R or B pixel j with green g0: the other of R and B from the
@@ -254,8 +239,8 @@ __device__ __forceinline__ uint32_t diag_at(const Raw& u, const Raw& d, const Gr
     const uint32_t gp = gat(gu, j + 1) + gat(gd, j - 1);
     const uint32_t dn = sad(n1, n2, absdiff(g2, gn));
     const uint32_t dp = sad(p1, p2, absdiff(g2, gp));
-    const int sn = (int)(n1 + n2 + g2) - (int)gn;
-    const int sp = (int)(p1 + p2 + g2) - (int)gp;
+    const int sn = dat(gu, j - 1) + dat(gd, j + 1) + (int)g2;
+    const int sp = dat(gu, j + 1) + dat(gd, j - 1) + (int)g2;
     return pick<1>(dn, dp, sn, sp);
 }
 
@@ -284,9 +269,8 @@ __device__ __forceinline__ void finish_row(bool red_row, const Raw& u, const Raw
             B[j] = red_row ? other : m.v[j];
         } else {                         // G pixel
             const uint32_t g0x2p1 = 2 * g0 + 1;
-            const uint32_t hor = pair_at(rat(m, j - 1), rat(m, j + 1), gat(gm, j - 1),
-                                         gat(gm, j + 1), g0x2p1);
-            const uint32_t ver = pair_at(u.v[j], d.v[j], gu.g[j], gd.g[j], g0x2p1);
+            const uint32_t hor = pair_at(dat(gm, j - 1), dat(gm, j + 1), g0x2p1);
+            const uint32_t ver = pair_at(gu.d[j], gd.d[j], g0x2p1);
             R[j] = red_row ? hor : ver;
             B[j] = red_row ? ver : hor;
         }
@@ -297,7 +281,7 @@ __device__ __forceinline__ void finish_row(bool red_row, const Raw& u, const Raw
 }
 
 // One band of rows [r0, r1) of one image, for the wave's 256 columns.
-template <bool EDGE, bool XCH>
+template <bool EDGE>
 __device__ __forceinline__ void run_band(const uint16_t* im, uint16_t* out, int H, int W, int r0,
                                          int r1, const Lane& ln) {
     const size_t plane = (size_t)H * (size_t)W;
@@ -317,24 +301,24 @@ __device__ __forceinline__ void run_band(const uint16_t* im, uint16_t* out, int 
         U[1] = unpack<EDGE>(fetch(r0), ln);
         U[2] = unpack<EDGE>(fetch(r0 + 1), ln);
         U[3] = unpack<EDGE>(fetch(r0 + 2), ln);
-        G[0] = green_row<EDGE, XCH>(true, a, b, U[0], U[1], U[2], ln);
-        G[1] = green_row<EDGE, XCH>(false, b, U[0], U[1], U[2], U[3], ln);
+        G[0] = green_row<EDGE>(true, a, b, U[0], U[1], U[2], ln);
+        G[1] = green_row<EDGE>(false, b, U[0], U[1], U[2], U[3], ln);
     }
-    // Two rows in flight: L[1] holds the odd rows after r0 + 2, L[0] the even.
-    Load L[2];
-    L[1] = fetch(r0 + 3);
-    L[0] = fetch(r0 + 4);
+    // Three rows in flight (106.5 us for 16 images, 109.5 with two): L[(x - r0)
+    // mod 3] holds raw row x; rows beyond r1 + 2 are never needed.
+    Load L[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) L[i] = fetch(min(r0 + 3 + i, r1 + 2));
     for (int base = r0; base < r1; base += 6) {
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
             const int r = base + k;
             if (r >= r1) break;
-            // Raw row r+3 arrives; row r+5 is loaded while this row and the
-            // next are computed (rows beyond r1 + 2 are never needed).
-            U[(k + 4) % 6] = unpack<EDGE>(L[(k + 1) % 2], ln);
-            if (r + 3 <= r1) L[(k + 1) % 2] = fetch(r + 5);
+            // Raw row r+3 arrives; row r+6 is loaded while the next rows are computed.
+            U[(k + 4) % 6] = unpack<EDGE>(L[k % 3], ln);
+            if (r + 4 <= r1) L[k % 3] = fetch(r + 6);
             const bool even = (k & 1) == 0;  // row r is an R row
-            G[(k + 2) % 6] = green_row<EDGE, XCH>(even, U[k], U[(k + 1) % 6], U[(k + 2) % 6],
+            G[(k + 2) % 6] = green_row<EDGE>(even, U[k], U[(k + 1) % 6], U[(k + 2) % 6],
                                              U[(k + 3) % 6], U[(k + 4) % 6], ln);
             finish_row(even, U[k], U[(k + 1) % 6], U[(k + 2) % 6], G[k], G[(k + 1) % 6],
                        G[(k + 2) % 6], out + (size_t)r * (size_t)W, plane, row_bytes, ln);
@@ -346,12 +330,11 @@ __global__ __launch_bounds__(256) void k_demosaic_gradient(const uint16_t* __res
                                                            uint16_t* __restrict__ rgb,
                                                            int32_t images, int32_t H, int32_t W,
                                                            int32_t band, int32_t bands,
-                                                           int32_t col_waves, int32_t exchange) {
+                                                           int32_t col_waves) {
     const int lane = threadIdx.x & 63;
     // Wave-uniform (scalar) from here: the wave index and everything derived from it.
-    __shared__ uint32_t xch[8];
-    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6)) + wv;
+    const int wave =
+        __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
     const int per_image = bands * col_waves;
     if (wave >= images * per_image) return;  // whole waves of the last block
     const int img = wave / per_image;
@@ -365,26 +348,15 @@ __global__ __launch_bounds__(256) void k_demosaic_gradient(const uint16_t* __res
     ln.ex_shift = lane == 0 ? 0u : 16u;
     ln.at_start = c0 == 0;
     ln.at_end = c0 + 4 == W;
-    ln.w = wv;
-    ln.xl = wv > 0;
-    ln.xr = wv < 3;
-    ln.xch = xch;
     const int r0 = bi * band;
     const int r1 = min(H, r0 + band);
     const size_t plane = (size_t)H * (size_t)W;
     const uint16_t* im = raw + (size_t)img * plane;
     uint16_t* out = rgb + (size_t)img * 3 * plane;
-    if (exchange) {
-        if (cw == 0 || cw == col_waves - 1)
-            run_band<true, true>(im, out, H, W, r0, r1, ln);
-        else
-            run_band<false, true>(im, out, H, W, r0, r1, ln);
-    } else {
-        if (cw == 0 || cw == col_waves - 1)
-            run_band<true, false>(im, out, H, W, r0, r1, ln);
-        else
-            run_band<false, false>(im, out, H, W, r0, r1, ln);
-    }
+    if (cw == 0 || cw == col_waves - 1)
+        run_band<true>(im, out, H, W, r0, r1, ln);
+    else
+        run_band<false>(im, out, H, W, r0, r1, ln);
 }
 
 }  // namespace
@@ -393,25 +365,38 @@ hipError_t launch_demosaic_gradient(const uint16_t* raw, int32_t images, int32_t
                                     uint16_t* rgb, int cus, hipStream_t stream) {
     cus = cus > 0 ? cus : 256;
     const int col_waves = (W / 4 + 63) / 64;
-    // Bands of about 16 waves per CU over the launch and at least 8 rows (each
-    // band re-reads 5 halo rows and recomputes 2 green rows; on one 2048 x 2048
-    // image 8-row bands still beat 16-row ones, which leave one wave per SIMD).
-    const int64_t target = (int64_t)16 * cus;
     const int64_t col_total = (int64_t)images * col_waves;
-    int64_t band = ((int64_t)H * col_total + target - 1) / target;
-    band = band < 8 ? 8 : (band > 128 ? 128 : band);
-    band = (band + 1) & ~(int64_t)1;  // whole Bayer rows
+    // A CU takes its bands' rows, and about 3 rows' work more for each (5 halo
+    // rows read and 2 green rows computed again): of the even band heights the
+    // one whose fullest CU has the least, in half rows, and half a band for the
+    // one that ends last (4 x 2048 x 2048: 24.8 us with 16 rows, 25.9 with 8; 1
+    // x 2398 x 2796: 14.5 with 14 rows, 15.8 with 8; 2 x 2048 x 2048: 12.4 with
+    // 16, 14.8 with 6 or 10).
+    // Launches that outgrow the 256 MiB cache take short bands, in the order of
+    // the rows: the waves that run at one time then read and write one stretch
+    // of each plane (16 x 2048 x 2048: 106.5 us with 10 rows, 114 with 64; 5.1
+    // against 4.7 TB/s). So do all whose rows do not start on 64-byte sectors,
+    // which the waves on both sides of a sector then write at about one time
+    // (13 x 1540 x 1608: 60 us with 6 rows, 63 with 8, 75 with 36).
+    const bool sectors = W % 32 == 0 && ((uintptr_t)rgb & 63u) == 0;
+    const bool large = (int64_t)images * H * W * 8 > ((int64_t)256 << 20);
+    int64_t band = 0, best = 0;
+    for (int64_t b = 6; b <= (!sectors ? 8 : large ? 10 : 32); b += 2) {
+        const int64_t blocks = (((int64_t)H + b - 1) / b * col_total + 3) / 4;
+        const int64_t per_cu = (blocks + cus - 1) / cus;
+        if (band && !sectors && per_cu > 8) continue;
+        const int64_t cost = 2 * per_cu * (b + 3) + b;
+        if (band && cost >= best) continue;
+        band = b;
+        best = cost;
+    }
+    // Well under 2^32 threads.
+    while (((int64_t)H + band - 1) / band * col_total >= (int64_t)1 << 25) band *= 2;
     const int bands = (int)(((int64_t)H + band - 1) / band);
     const int64_t waves = col_total * bands;
     const int64_t blocks = (waves + 3) / 4;
-    // The LDS exchange needs every workgroup inside one band (whole groups of
-    // 4 column waves). Its barriers cost more than they save on launches of
-    // up to 8 waves per CU (one 2048 x 2048 image in 8-row bands, 8 waves per
-    // CU: 9.6 vs 9.0 us), and save about 4 % on large ones (16 images: 101 vs
-    // 106 us).
-    const int exchange = (col_waves % 4 == 0 && waves > 8 * (int64_t)cus) ? 1 : 0;
     hipLaunchKernelGGL(k_demosaic_gradient, dim3((unsigned)blocks), dim3(256), 0, stream, raw, rgb,
-                       images, H, W, (int)band, bands, col_waves, exchange);
+                       images, H, W, (int)band, bands, col_waves);
     return hipGetLastError();
 }
 
