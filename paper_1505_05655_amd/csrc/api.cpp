@@ -215,11 +215,14 @@ bool balanced_tiling(int64_t lines, int32_t detectors, int32_t bands, int vec, i
 //    + drift min(1, lines per tile / 20000)): neighbouring strips share the
 //    memory sectors at their ends, the more often fetched twice the further
 //    their tiles have drifted apart (more so where the lanes of a line do not
-//    divide a wave);
+//    divide a wave), and every sector where a strip is narrower than one;
 //  - one round of tiles (at most one per CU) stages, then streams; more tiles
 //    overlap the two, but their streams, far apart in the image, run at a
 //    fraction of the rate, which only a scene with fewer lines than levels
 //    makes up for.
+// A tile of fewer lines than a pass takes has fewer pixels per lane: 1 x 1024
+// x 1024 in 256 tiles of 16 x 256, 6.3 us with 4 and 7.3 with 8; in 128 of 8 x
+// 1024, 7.6; 1 x 512 x 512 5.25 with 2, 5.75 with 8.
 // Rows that start on 64-byte sectors (D a multiple of 32) take power-of-two
 // strips and other multiples of 64 (whole 128-byte lines, see check_plan), any
 // other rows power-of-two strips and even divisions of the row into about 256
@@ -283,13 +286,18 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
         const double w = std::min(width, detectors);
         const int64_t tiles = strips * bands * k;
         const double per_tile = (double)lines / (double)k;
-        // Lines a pass takes, and the share of the last one's that exist.
-        const int lanes = std::max(1, width / 8);
+        // 8 pixels per lane, or fewer (of 4 lines too) where a pass, the lines
+        // that all lanes take at once, would not be filled by the tile's.
+        int vec = std::min(std::min(vmax, 8), W);
+        while (!even && vmax >= 8 && vec > 2 && p.threads / (W / vec) * 4 > per_tile) vec >>= 1;
+        const int lanes = std::max(1, width / (vmax >= 8 ? vec : 8));
         const double pass = (double)std::max(1, p.threads / lanes) * 4.0;
         const double waste = std::min(1.5, std::ceil(per_tile / pass) * pass / per_tile);
         const double drift = m.drift * std::min(1.0, per_tile / 20000.0) *
                              (even && 64 % lanes != 0 ? m.ragged : 1.0);
-        const double eff = w / (w + m.ends + drift);
+        // Segments of less than a 64-byte sector.
+        const double part = sectors && w < 32.0 ? std::pow(w / 32.0, 0.7) : 1.0;
+        const double eff = part * w / (w + m.ends + drift);
         const bool one_round = tiles <= cus;
         const double rate = one_round ? std::min(6e6 * eff, m.per_tile * (double)tiles)
                                       : m.overlapped * eff;  // bytes per us
@@ -314,8 +322,8 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
             p.strip = W;
             p.strips = even ? (int32_t)strips : 0;
             p.lane_map = even ? 1 : 0;
-            p.vec = std::min(std::min(vmax, 8), W);
-            p.unroll = p.vec == 8 ? 4 : 8;
+            p.vec = vec;
+            p.unroll = vmax >= 8 || vec == 8 ? 4 : 8;
             p.chunk_lines = (int32_t)std::min<int64_t>((lines + k - 1) / k, INT32_MAX);
         }
     };

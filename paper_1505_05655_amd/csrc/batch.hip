@@ -96,7 +96,7 @@ __device__ __forceinline__ void batch_tile_vec(const BatchReq& q, const BatchTil
 // threads and 8 bytes the CU had 4 times the bytes in flight, and neighbouring
 // strips fetched the sectors they share again) while the other evaluates its
 // strip. 16 requests of 512 to 8192 lines and detectors, 1 to 4 bands, 10 and
-// 12 bit: 1.97 -> 1.85 ms from that, 8 pixels per lane on any row and dense
+// 12 bit: 1.97 -> 1.75 ms from that, 8 pixels per lane on any row and dense
 // strips of 128 detectors for 4096 levels (packed: 64).
 __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void k_apply_batch(const BatchReq* __restrict__ reqs, const BatchTile* __restrict__ tiles,

@@ -13,10 +13,10 @@
 // detector's n samples are read with loads that are coalesced across the wave
 // (consecutive detectors), 8 points at a time and 8 ahead: with one load per
 // point and iteration the kernel was a chain of n memory latencies (17.6 us
-// for 4 x 48 x 12000, order 3; 8.6 us now; 16 at a time: 12.7). The band's targets are wave-uniform,
-// and the (M+1) x (2M+2) system stays in registers
-// (every index below is a compile-time constant after unrolling; the pivot
-// row swap is a select, not an indexed access).
+// for 4 x 48 x 12000, order 3; 7.9 us now; 16 at a time: 12.7). The band's
+// targets are wave-uniform, and the (M+1) x (2M+2) system stays in registers
+// (every index below is a compile-time constant after unrolling; the pivot row
+// swap is a select, not an indexed access).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>

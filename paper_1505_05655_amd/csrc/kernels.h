@@ -57,7 +57,8 @@ hipError_t launch_lut_build_ws(const double* coeffs, int64_t rows, int32_t detec
                                int32_t levels, uint16_t* lut, uint64_t* planes, int16_t* heads,
                                int xcds, hipStream_t stream);
 
-// lut_build: one thread per 8 consecutive levels of one LUT row.
+// LUT build: waves evaluate rows of 512 levels or more, a thread 8 consecutive
+// levels of shorter ones.
 hipError_t launch_lut_build(const double* coeffs, int64_t rows, int32_t levels, uint16_t* lut,
                             hipStream_t stream);
 

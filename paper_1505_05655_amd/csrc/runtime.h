@@ -30,7 +30,7 @@ rc_status hip_fail(hipError_t e);
 
 // Largest VEC (1, 2, 4, or 8 when cap >= 8) the image pointers and the
 // detector count allow. The plain correction kernels take up to 8 pixels per
-// lane, the persistent batch kernel up to 4.
+// lane; the plan cache's batch entries are keyed by the bound at 4.
 int max_vec(const uint16_t* dn, const uint16_t* out, int32_t detectors, int cap = 4);
 
 // Launch shape with power-of-two strips of W detectors and about two rounds

@@ -96,3 +96,24 @@ def test_evenly_divided_rows(lines, D, L, off):
     torch.cuda.synchronize()
     np.testing.assert_array_equal(src.host(), want)
     src.check_pads()
+
+
+# Tiles with fewer lines than a pass of 8 pixels per lane takes: 2 or 4 pixels per lane.
+@pytest.mark.parametrize("B,lines,D,L", [(1, 1024, 1024, 1024), (1, 512, 512, 1024),
+                                         (1, 700, 600, 1024), (4, 599, 640, 1024),
+                                         (1, 401, 800, 4096), (1, 31, 8000, 700), (2, 1, 64, 16)])
+def test_few_lines_per_tile(B, lines, D, L):
+    assert rc.rc_plan_for(lines, D, B, L)[0].as_dict()["vec"] in (2, 4)
+    coeffs, dn = pins.tiny_case(D + lines, B, lines, D, L)
+    o = oracle.get()
+    lut = o.lut_build(coeffs, L)
+    want = o.correct(dn, lut)
+    d_lut = to_dev_u16(lut)
+    src = Guarded((B, lines, D))
+    src.t.copy_(to_dev_u16(dn).view(B, lines, D))
+    out = Guarded((B, lines, D))
+    for dst in (out, src):  # apart, then in place
+        rc.rc_correct(src.t, d_lut, lines, D, B, L, dst.t)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(dst.host(), want)
+        dst.check_pads()
