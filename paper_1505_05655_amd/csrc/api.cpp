@@ -348,7 +348,17 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
         }
     // Non-temporal stores gain 2-8 % where every segment is whole 64-byte
     // sectors and lose up to 25 % where neighbouring tiles complete them.
-    p.nontemporal = detectors % 32 == 0 && p.strip >= 32 ? 2 : 0;
+    // Non-temporal loads too for images of one to four times the 256 MiB cache,
+    // whose reads then push out less of what is still being written back (4 x
+    // 4000 x 8000, build and correction: 125 -> 119 us; 2 x 20000 x 4096 141 ->
+    // 136; 2 x 8000 x 6016 87 -> 85). Smaller images lose what they find there
+    // (1 x 6000 x 2048 28 -> 38), larger ones 3 % (4 x 12000 x 12000 448 ->
+    // 461, 3 x 12000 x 8640 at 4096 levels 329 -> 341), except right after a
+    // large write to other memory (the first of these 500 -> 465).
+    const double cache = 256.0 * 1048576.0;
+    p.nontemporal = detectors % 32 != 0 || p.strip < 32      ? 0
+                    : image > cache && image <= 4.0 * cache ? 1
+                                                            : 2;
     if (found) *plan = p;
     last = Last{&di, lines, detectors, bands, levels, vmax, in_place, found, p};
     return found;
