@@ -275,7 +275,8 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
     double best = 0.0;
     bool found = false;
     const double image = 4.0 * (double)bands * (double)lines * (double)detectors;
-    const int64_t cap = max_chunk_lines(detectors, p.threads, 8);
+    // Fewer pixels per lane than 8 may raise the thread count below.
+    const int64_t cap = max_chunk_lines(detectors, vmax >= 8 ? p.threads : 1024, 8);
     if (cap < 1) return false;
     const int64_t kmin = std::max<int64_t>(1, (lines + cap - 1) / cap);
     // Strips of `width` detectors with k line chunks; even: S of nearly equal
@@ -359,6 +360,9 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
     p.nontemporal = detectors % 32 != 0 || p.strip < 32      ? 0
                     : image > cache && image <= 4.0 * cache ? 1
                                                             : 2;
+    // The plan runs as it is too (rc_correct_plan, in place): a lane for each
+    // vec of the strip's detectors. widen_plan takes this back.
+    while (found && p.strip / p.vec > p.threads) p.threads *= 2;
     if (found) *plan = p;
     last = Last{&di, lines, detectors, bands, levels, vmax, in_place, found, p};
     return found;
@@ -589,6 +593,7 @@ bool widen_plan(const uint16_t* dn, const uint16_t* out, int32_t detectors, rc_p
     }
     // In place, the lanes that share pixels have to be in one wave.
     if (dn == out && (p.lane_map != 0 || p.strip > 512)) return false;
+    if (p.strip / p.vec == p.threads) p.threads = 256;
     p.vec = 8;
     p.unroll = 4;
     *plan = p;

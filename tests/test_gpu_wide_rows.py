@@ -117,3 +117,24 @@ def test_few_lines_per_tile(B, lines, D, L):
         torch.cuda.synchronize()
         np.testing.assert_array_equal(dst.host(), want)
         dst.check_pads()
+
+
+@pytest.mark.parametrize("B,lines,D", [(4, 20000, 6003), (4, 12000, 9999)])
+def test_the_reported_plan_of_wide_strips(B, lines, D):
+    """A plan whose strip has more detectors than 256 lanes of one pixel: rc_correct_plan takes it,
+    with rc_correct's result."""
+    L = 1024
+    plan, _ = rc.rc_plan_for(lines, D, B, L)
+    p = plan.as_dict()
+    assert p["vec"] == 1 and p["strip"] > 256
+    g = torch.Generator(device="cuda:0").manual_seed(D)
+    src = torch.randint(0, 1200, (B, lines, D), generator=g, device="cuda:0", dtype=torch.int16)
+    lut = torch.randint(0, 1024, (B, D, L), generator=g, device="cuda:0", dtype=torch.int16)
+    want, out = torch.empty_like(src), torch.empty_like(src)
+    rc.rc_correct(src, lut, lines, D, B, L, want)
+    rc.rc_correct_plan(src, lut, lines, D, B, L, out, plan)
+    assert torch.equal(out, want)
+    at = torch.randint(0, lines, (64,), generator=g, device="cuda:0")
+    rows = src[:, at].long().clamp(max=L - 1)
+    picked = torch.gather(lut.transpose(1, 2).contiguous(), 1, rows)
+    assert torch.equal(picked, want[:, at])
