@@ -192,9 +192,7 @@ __global__ __launch_bounds__(256) void k_demosaic(const uint16_t* __restrict__ r
 
 }  // namespace
 
-hipError_t launch_demosaic(const uint16_t* raw, int32_t images, int32_t H, int32_t W,
-                           uint16_t* rgb, int cus, hipStream_t stream) {
-    const int col_waves = (W / 4 + 63) / 64;
+int64_t demosaic_band(int32_t images, int32_t H, int32_t W, bool sectors, int cus) {
     // Short bands, in the order of the rows: the waves that run at one time
     // then read and write one stretch of each plane. Long bands, 8 to 12
     // streams per CU all over the images, were slower: 16 x 2048 x 2048 99 us
@@ -204,17 +202,26 @@ hipError_t launch_demosaic(const uint16_t* raw, int32_t images, int32_t H, int32
     // 2048: 27.3 us with 8, 28.6 with 4); small ones take about 12 waves per CU
     // (one such image in 6-row bands: 6.9 us, 7.5 with 4).
     if (cus <= 0) cus = 256;
-    const int64_t col_total = (int64_t)images * col_waves;
-    const bool sectors = W % 32 == 0 && ((uintptr_t)rgb & 63u) == 0;
+    const int64_t col_total = (int64_t)images * ((W / 4 + 63) / 64);
     const int64_t target = (int64_t)12 * cus;
     int64_t band = ((int64_t)H * col_total + target - 1) / target;
     band = !sectors ? 2 : band < 4 ? 4 : band > 8 ? 8 : band;
     band = (band + 1) & ~(int64_t)1;  // whole Bayer rows
-    // Well under 2^32 threads.
-    while (((int64_t)H + band - 1) / band * col_total >= (int64_t)1 << 25) band *= 2;
+    // Well under 2^32 threads, where the images alone do not take as many (a
+    // band of the whole height is the longest).
+    while (band < H && ((int64_t)H + band - 1) / band * col_total >= (int64_t)1 << 25) band *= 2;
+    return band;
+}
+
+hipError_t launch_demosaic(const uint16_t* raw, int32_t images, int32_t H, int32_t W,
+                           uint16_t* rgb, int cus, hipStream_t stream) {
+    const int col_waves = (W / 4 + 63) / 64;
+    const bool sectors = W % 32 == 0 && ((uintptr_t)rgb & 63u) == 0;
+    const int64_t band = demosaic_band(images, H, W, sectors, cus);
     const int bands = (int)(((int64_t)H + band - 1) / band);
-    const int64_t waves = col_total * bands;
+    const int64_t waves = (int64_t)images * col_waves * bands;
     const int64_t blocks = (waves + 3) / 4;
+    if (blocks * 256 > (int64_t)UINT32_MAX) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(k_demosaic, dim3((unsigned)blocks), dim3(256), 0, stream, raw, rgb, images,
                        H, W, (int)band, bands, col_waves);
     return hipGetLastError();

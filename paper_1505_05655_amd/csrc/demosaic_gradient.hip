@@ -361,11 +361,9 @@ __global__ __launch_bounds__(256) void k_demosaic_gradient(const uint16_t* __res
 
 }  // namespace
 
-hipError_t launch_demosaic_gradient(const uint16_t* raw, int32_t images, int32_t H, int32_t W,
-                                    uint16_t* rgb, int cus, hipStream_t stream) {
+int64_t demosaic_gradient_band(int32_t images, int32_t H, int32_t W, bool sectors, int cus) {
     cus = cus > 0 ? cus : 256;
-    const int col_waves = (W / 4 + 63) / 64;
-    const int64_t col_total = (int64_t)images * col_waves;
+    const int64_t col_total = (int64_t)images * ((W / 4 + 63) / 64);
     // A CU takes its bands' rows, and about 3 rows' work more for each (5 halo
     // rows read and 2 green rows computed again): of the even band heights the
     // one whose fullest CU has the least, in half rows, and half a band for the
@@ -378,7 +376,6 @@ hipError_t launch_demosaic_gradient(const uint16_t* raw, int32_t images, int32_t
     // against 4.7 TB/s). So do all whose rows do not start on 64-byte sectors,
     // which the waves on both sides of a sector then write at about one time
     // (13 x 1540 x 1608: 60 us with 6 rows, 63 with 8, 75 with 36).
-    const bool sectors = W % 32 == 0 && ((uintptr_t)rgb & 63u) == 0;
     const bool large = (int64_t)images * H * W * 8 > ((int64_t)256 << 20);
     int64_t band = 0, best = 0;
     for (int64_t b = 6; b <= (!sectors ? 8 : large ? 10 : 32); b += 2) {
@@ -390,11 +387,21 @@ hipError_t launch_demosaic_gradient(const uint16_t* raw, int32_t images, int32_t
         band = b;
         best = cost;
     }
-    // Well under 2^32 threads.
-    while (((int64_t)H + band - 1) / band * col_total >= (int64_t)1 << 25) band *= 2;
+    // Well under 2^32 threads, where the images alone do not take as many (a
+    // band of the whole height is the longest).
+    while (band < H && ((int64_t)H + band - 1) / band * col_total >= (int64_t)1 << 25) band *= 2;
+    return band;
+}
+
+hipError_t launch_demosaic_gradient(const uint16_t* raw, int32_t images, int32_t H, int32_t W,
+                                    uint16_t* rgb, int cus, hipStream_t stream) {
+    const int col_waves = (W / 4 + 63) / 64;
+    const bool sectors = W % 32 == 0 && ((uintptr_t)rgb & 63u) == 0;
+    const int64_t band = demosaic_gradient_band(images, H, W, sectors, cus);
     const int bands = (int)(((int64_t)H + band - 1) / band);
-    const int64_t waves = col_total * bands;
+    const int64_t waves = (int64_t)images * col_waves * bands;
     const int64_t blocks = (waves + 3) / 4;
+    if (blocks * 256 > (int64_t)UINT32_MAX) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(k_demosaic_gradient, dim3((unsigned)blocks), dim3(256), 0, stream, raw, rgb,
                        images, H, W, (int)band, bands, col_waves);
     return hipGetLastError();
@@ -417,7 +424,8 @@ rc_status rc_demosaic_gradient(const uint16_t* raw, int32_t images, int32_t heig
     if (!raw || !rgb) return RC_EINVAL;
     if (((uintptr_t)raw | (uintptr_t)rgb) & 7u) return RC_EINVAL;
     if (overlaps(raw, (size_t)n * 2, rgb, (size_t)n * 6)) return RC_EINVAL;
-    // Wave indices are 32-bit: images x bands x column waves < 2^31 (bands of >= 8 rows).
+    // Wave indices are 32-bit: images x bands x column waves < 2^31 (bands of 8
+    // rows; of fewer only where that makes less than 2^25 waves).
     if ((int64_t)images * (height / 8 + 1) * ((width / 4 + 63) / 64) >= ((int64_t)1 << 31))
         return RC_EINVAL;
     const DeviceInfo* di = current_device();

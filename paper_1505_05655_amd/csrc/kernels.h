@@ -66,6 +66,11 @@ hipError_t launch_lut_build(const double* coeffs, int64_t rows, int32_t levels, 
 hipError_t launch_fit(const double* x, const double* y, int32_t bands, int32_t points,
                       int32_t detectors, int32_t order, double* coeffs, hipStream_t stream);
 
+// Rows per band of the two demosaicing kernels (even; the last band of an image
+// may be shorter). sectors: the rows of rgb start on 64-byte sectors.
+int64_t demosaic_band(int32_t images, int32_t H, int32_t W, bool sectors, int cus);
+int64_t demosaic_gradient_band(int32_t images, int32_t H, int32_t W, bool sectors, int cus);
+
 // Bilinear Bayer demosaicing (arguments validated by rc_demosaic).
 hipError_t launch_demosaic(const uint16_t* raw, int32_t images, int32_t H, int32_t W,
                            uint16_t* rgb, int cus, hipStream_t stream);
