@@ -275,8 +275,10 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
     double best = 0.0;
     bool found = false;
     const double image = 4.0 * (double)bands * (double)lines * (double)detectors;
-    // Fewer pixels per lane than 8 may raise the thread count below.
-    const int64_t cap = max_chunk_lines(detectors, vmax >= 8 ? p.threads : 1024, 8);
+    // Most lines a tile may have; strips of more lanes than that many threads
+    // have a lower bound of their own (consider).
+    const int unroll = vmax >= 8 ? 4 : 8;
+    const int64_t cap = max_chunk_lines(detectors, p.threads, unroll);
     if (cap < 1) return false;
     const int64_t kmin = std::max<int64_t>(1, (lines + cap - 1) / cap);
     // Strips of `width` detectors with k line chunks; even: S of nearly equal
@@ -291,6 +293,11 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
         // that all lanes take at once, would not be filled by the tile's.
         int vec = std::min(std::min(vmax, 8), W);
         while (!even && vmax >= 8 && vec > 2 && p.threads / (W / vec) * 4 > per_tile) vec >>= 1;
+        // What check_plan refuses: offsets beyond 32 bits, a launch of 2^32 threads.
+        int threads = p.threads;
+        while (W / vec > threads) threads *= 2;
+        if ((lines + k - 1) / k > max_chunk_lines(detectors, threads, unroll)) return;
+        if (tiles > cus && tiles * threads >= (int64_t)1 << 32) return;
         const int lanes = std::max(1, width / (vmax >= 8 ? vec : 8));
         const double pass = (double)std::max(1, p.threads / lanes) * 4.0;
         const double waste = std::min(1.5, std::ceil(per_tile / pass) * pass / per_tile);
@@ -324,7 +331,7 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
             p.strips = even ? (int32_t)strips : 0;
             p.lane_map = even ? 1 : 0;
             p.vec = vec;
-            p.unroll = vmax >= 8 || vec == 8 ? 4 : 8;
+            p.unroll = unroll;
             p.chunk_lines = (int32_t)std::min<int64_t>((lines + k - 1) / k, INT32_MAX);
         }
     };

@@ -1,7 +1,9 @@
 // Host-side choices of librc (launch shapes, plans, strips) by their internal names, for tests
 // that need no GPU. Each line of standard input is a command; each gives one line of output.
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
+#include <cstring>
 #include <iostream>
 #include <sstream>
 #include <string>
@@ -22,12 +24,64 @@ static void demosaic(std::istringstream& in) {
     std::printf("%lld\n", (long long)band);
 }
 
+static DeviceInfo mi355x() {
+    DeviceInfo di;
+    di.cus = 256;
+    di.xcds = 8;
+    di.lds = di.lds_per_cu = 160 * 1024;
+    di.arch = "probe";
+    return di;
+}
+
+static bool runs(const rc_plan& p, int64_t N, int D, int B, int L, int vmax, const DeviceInfo& di,
+                 bool wide = false) {
+    ApplyParams a{};
+    size_t lds = 0;
+    return check_plan(p, N, D, B, L, vmax, di, &a, &lds, wide) == RC_OK;
+}
+
+// plan B N D L dn_offset out_offset (bytes; -1: in place): whether the plan rc_correct takes for
+// the shape can run; whether power-of-two strips (pow2_plan) or, where those are LDS strips, one
+// equal tile per CU (balanced_tiling) can.
+static void plan(std::istringstream& in) {
+    int64_t N;
+    int B, D, L, dn_off, out_off;
+    in >> B >> N >> D >> L >> dn_off >> out_off;
+    const DeviceInfo di = mi355x();
+    const uint16_t* dn = (const uint16_t*)(uintptr_t)((1ull << 40) + dn_off);
+    const uint16_t* out =
+        out_off < 0 ? dn : (const uint16_t*)(uintptr_t)((1ull << 45) + out_off);
+    const int vmax = max_vec(dn, out, D, 8);
+    rc_plan p, w;
+    default_plan(N, D, B, L, vmax, di, &p, dn == out);
+    w = p;
+    const bool ok = (vmax < 8 && widen_plan(dn, out, D, &w) && runs(w, N, D, B, L, vmax, di, true)) ||
+                    runs(p, N, D, B, L, vmax, di);
+    rc_plan q;
+    pow2_plan(N, D, B, L, vmax, di, &q);
+    const bool pow2 = runs(q, N, D, B, L, vmax, di);
+    const bool lds = q.path != RC_PATH_L2;
+    std::memset(&q, 0, sizeof q);
+    q.path = L >= 512 ? RC_PATH_PACKED : RC_PATH_LDS;
+    q.vec = std::min(vmax, 2);
+    q.threads = 256;
+    q.unroll = 8;
+    q.xcd_remap = q.lane_map = 1;
+    const int wmax = widest_strip(q.path, L, di.lds);
+    const bool even = lds && wmax >= 16 &&
+                      balanced_tiling(N, D, B, q.vec, wmax, di.cus, q.threads, q.unroll, &q.strips,
+                                      &q.strip, &q.chunk_lines) &&
+                      runs(q, N, D, B, L, vmax, di);
+    std::printf("%d %d %d\n", ok, pow2, even);
+}
+
 int main() {
     std::string line, cmd;
     while (std::getline(std::cin, line)) {
         std::istringstream in(line);
         in >> cmd;
         if (cmd == "demosaic") demosaic(in);
+        else if (cmd == "plan") plan(in);
         else return 1;
         std::fflush(stdout);
     }
