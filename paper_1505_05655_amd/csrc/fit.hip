@@ -40,28 +40,30 @@ __device__ __forceinline__ void fit_one(const double* __restrict__ x,
     for (int k = 0; k <= M; ++k) T[k] = 0.0;
     const double* xb = x + (size_t)b * (size_t)points * (size_t)detectors + (size_t)d;
     const double* yb = y + (size_t)b * (size_t)points;
-    constexpr int U = 8;
+    constexpr uint32_t U = 8;
     double xs[U], ys[U];
-    auto load = [&](int i0) {
+    // Unsigned: the last rounds of 2^31 - 1 points look past INT32_MAX.
+    const uint32_t n = (uint32_t)points;
+    auto load = [&](uint32_t i0) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = min(i0 + u, points - 1);  // past the last point: not used
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t i = min(i0 + u, n - 1);  // past the last point: not used
             xs[u] = xb[(size_t)i * (size_t)detectors];
             ys[u] = yb[i];
         }
     };
     load(0);
-    for (int i0 = 0; i0 < points; i0 += U) {
+    for (uint32_t i0 = 0; i0 < n; i0 += U) {
         double xc[U], yc[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (uint32_t u = 0; u < U; ++u) {
             xc[u] = xs[u];
             yc[u] = ys[u];
         }
-        if (i0 + U < points) load(i0 + U);
+        if (i0 + U < n) load(i0 + U);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (i0 + u >= points) break;  // uniform
+        for (uint32_t u = 0; u < U; ++u) {
+            if (i0 + u >= n) break;  // uniform
             double p = 1.0;  // x_i^k
 #pragma unroll
             for (int k = 0; k <= 2 * M; ++k) {
