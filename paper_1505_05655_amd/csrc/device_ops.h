@@ -443,6 +443,11 @@ __device__ __forceinline__ uint32_t pk_add(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, a) +
                                                 __builtin_bit_cast(u16x2, b)));
 }
+__device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t,
+                              __builtin_elementwise_max(__builtin_bit_cast(u16x2, a),
+                                                        __builtin_bit_cast(u16x2, b)));
+}
 // (As an instruction: the compiler turns a minimum with 1 into a comparison
 // per half.)
 __device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
@@ -536,6 +541,7 @@ __device__ __forceinline__ void encode_pass(const u32x4 w, int L, int blk, bool 
             m[i] = pk_sub(0u, up & pk_min(pk_sub(top2, w[i]), kOnes)) & vm;
             any |= d[i] & m[i];
             wrong |= d[i] & ~m[i] & vm;
+            wrong |= pk_max(w[i], top2) ^ top2;  // an entry above L-1
             zeros = pk_add(zeros, (kOnes - up) & vm);
         }
         const uint32_t two = group8_or((any | (any >> 16)) & 2u);
@@ -547,7 +553,7 @@ __device__ __forceinline__ void encode_pass(const u32x4 w, int L, int blk, bool 
             x[i] = (pk_sub(d[i], ss) & m[i]) | (kOnes & ~m[i]);
             wrong |= x[i] & ~kOnes;
         }
-        ok = group8_ok(wrong != 0 || first > top || last > top, lane);
+        ok = group8_ok(wrong != 0, lane);
         lo8 = step_byte(x[0], x[1], x[2], x[3], q);
         // A block that opens with zeros: as many steps below 0 as steps end in 0.
         const int nz = (int)group8_add((zeros & 0xffffu) + (zeros >> 16));
