@@ -46,11 +46,19 @@ struct BatchReq {
     int32_t pad;
 };
 
-// First detector of strip s (the last strip of a request with 8 pixels per
-// lane has at least 8 detectors: it starts inside the one before it).
-inline int32_t strip_start(const BatchReq& q, int32_t s) {
+// First detector of strip s, and the width of the strip that starts at d0.
+// Where the rest of a row is less than the 8 detectors a lane takes, the last
+// strip takes what it lacks from the one before it, so that strips stay apart
+// (a request may be corrected in place); strips of 8 overlap instead.
+constexpr int32_t strip_start(const BatchReq& q, int32_t s) {
     const int32_t d0 = s << q.log_strip;
     return q.vec == 8 && q.detectors - d0 < 8 ? q.detectors - 8 : d0;
+}
+constexpr int32_t strip_width(const BatchReq& q, int32_t d0) {
+    const int32_t W = 1 << q.log_strip;
+    const int32_t after = q.detectors - d0 - W;
+    if (q.vec == 8 && W > 8 && after > 0 && after < 8) return W - (8 - after);
+    return after < 0 ? W + after : W;
 }
 
 struct BatchTile {
@@ -84,8 +92,8 @@ hipError_t prepare_batch_kernel(size_t lds);
 
 // Fills q's strip shape and mode from a plan, fitted to the persistent
 // kernel's workgroup size and LDS budget; 8 pixels per lane whatever the rows'
-// alignment, except for a request in place whose last strip would have to
-// overlap the one before it, and for fewer than 8 detectors.
+// alignment, except for fewer than 8 detectors, and in place where strips of 8
+// would have to overlap.
 void fit_request_plan(const rc_plan& plan, int levels, size_t lds_cap, BatchReq* q);
 
 }  // namespace rc

@@ -71,8 +71,7 @@ template <int VEC>
 __device__ __forceinline__ void batch_tile_vec(const BatchReq& q, const BatchTile& tl,
                                                void* smem) {
     constexpr int U = VEC == 8 ? kBatchUnroll8 : kBatchUnroll;
-    const int W = 1 << q.log_strip;
-    const int weff = min(W, q.detectors - tl.d0);
+    const int weff = strip_width(q, tl.d0);
     if (q.fused) {
         const bool write_lut = tl.n0 == 0;
         auto run = [&](auto mode) {
@@ -184,13 +183,11 @@ void fit_request_plan(const rc_plan& plan_in, int levels, size_t lds_cap, BatchR
     if (p.path != RC_PATH_L2 && plan_lds_bytes(p.path, p.strip, levels) > lds_cap)
         p.path = RC_PATH_L2;
     // In place, a line's overlapping lanes share a wave (strips of at most 512
-    // detectors), but overlapping strips would correct pixels twice.
-    const int rest = q->detectors % p.strip;
+    // detectors), and strips may not overlap (strip_width).
     const bool in_place = q->dn == q->out;
-    p.vec = p.strip >= 8 && q->detectors >= 8 &&
-                    !(in_place && ((rest > 0 && rest < 8) || p.strip > 512))
-                ? 8
-                : 1;
+    if (in_place) p.strip = std::min(p.strip, 512);
+    const int rest = q->detectors % p.strip;
+    p.vec = p.strip >= 8 && q->detectors >= 8 && !(in_place && p.strip == 8 && rest > 0) ? 8 : 1;
     while (p.strip / p.vec > kBatchStream) p.strip >>= 1;
     int lw = 0;
     while ((1 << (lw + 1)) <= p.strip) ++lw;

@@ -8,6 +8,7 @@
 #include <sstream>
 #include <string>
 
+#include "batch.h"
 #include "kernels.h"
 #include "runtime.h"
 
@@ -75,6 +76,28 @@ static void plan(std::istringstream& in) {
     std::printf("%d %d %d\n", ok, pow2, even);
 }
 
+// strips D L path W in_place: pixels per lane of a batch request with strips planned W wide, then
+// first detector and width of each strip.
+static void strips(std::istringstream& in) {
+    rc_plan p;
+    std::memset(&p, 0, sizeof p);
+    BatchReq q;
+    std::memset(&q, 0, sizeof q);
+    int in_place;
+    in >> q.detectors >> q.levels >> p.path >> p.strip >> in_place;
+    p.vec = 1;
+    q.dn = (const uint16_t*)(uintptr_t)(1ull << 40);
+    q.out = in_place ? (uint16_t*)q.dn : (uint16_t*)(uintptr_t)(1ull << 45);
+    fit_request_plan(p, q.levels, kBatchLds, &q);
+    std::printf("%d", q.vec);
+    const int W = 1 << q.log_strip;
+    for (int s = 0; s * W < q.detectors; ++s) {
+        const int d0 = strip_start(q, s);
+        std::printf(" %d %d", d0, strip_width(q, d0));
+    }
+    std::printf("\n");
+}
+
 int main() {
     std::string line, cmd;
     while (std::getline(std::cin, line)) {
@@ -82,6 +105,7 @@ int main() {
         in >> cmd;
         if (cmd == "demosaic") demosaic(in);
         else if (cmd == "plan") plan(in);
+        else if (cmd == "strips") strips(in);
         else return 1;
         std::fflush(stdout);
     }
