@@ -11,16 +11,14 @@
 
 namespace rc {
 
-constexpr int kBatchThreads = 512;
+constexpr int kBatchThreads = 1024;
 // Threads of a workgroup that stream the image; all build the LUT strip.
 constexpr int kBatchStream = 256;
-// Lines per register set with 8 pixels per lane, and with 1 (bounds the
-// prefetch overshoot of either).
-constexpr int kBatchUnroll8 = 4;
-constexpr int kBatchUnroll = 8;
+// Lines per register set.
+constexpr int kBatchUnroll = 4;
 constexpr size_t kBatchLds = 80 * 1024;
-// Resident workgroups per CU the batch launch aims for (two 80 KiB strips).
-constexpr int kBatchPerCu = 2;
+// Resident workgroups per CU (1024 threads of up to 128 registers).
+constexpr int kBatchPerCu = 1;
 // Tile queues of the persistent kernel: one per XCD (workgroups are dispatched
 // to the XCDs round-robin, so workgroup i starts on queue i % kBatchQueues).
 constexpr int kBatchQueues = 8;

@@ -12,8 +12,7 @@
 //     then helps with the others. For every other request a tile is fused: it
 //     evaluates its strip's LUT rows from the coefficients straight into LDS
 //     (the first line chunk of a strip also writes them to the request's LUT),
-//     then corrects its lines, so the LUT is never read back from memory and the
-//     binary64 evaluation of one workgroup overlaps the streaming of others.
+//     then corrects its lines, so the LUT is never read back from memory.
 //     The strips of one request line chunk stay together on one queue,
 //     groups are dealt longest first, so the tail of the batch is made of
 //     short tiles. The last workgroup to finish resets the counters, so a
@@ -70,12 +69,11 @@ __global__ __launch_bounds__(256) void k_lut_build_batch(const BatchReq* __restr
 template <int VEC>
 __device__ __forceinline__ void batch_tile_vec(const BatchReq& q, const BatchTile& tl,
                                                void* smem) {
-    constexpr int U = VEC == 8 ? kBatchUnroll8 : kBatchUnroll;
     const int weff = strip_width(q, tl.d0);
     if (q.fused) {
         const bool write_lut = tl.n0 == 0;
         auto run = [&](auto mode) {
-            fused_tile<VEC, U, decltype(mode)::value>(
+            fused_tile<VEC, kBatchUnroll, decltype(mode)::value>(
                 q.coeffs, q.dn, q.lut, q.out, q.lines, q.detectors, q.levels, q.log_strip, tl.band,
                 tl.d0, weff, tl.n0, tl.n1, write_lut, smem, q.lut_vec != 0, kBatchStream);
         };
@@ -83,21 +81,24 @@ __device__ __forceinline__ void batch_tile_vec(const BatchReq& q, const BatchTil
         else if (q.mode == kDense) run(std::integral_constant<int, kDense>{});
         else run(std::integral_constant<int, kRaw>{});
     } else {
-        apply_tile<VEC, U, 0, kGlobal>(q.dn, q.lut, q.out, q.lines, q.detectors, q.levels,
-                                       q.log_strip, tl.band, tl.d0, weff, tl.n0, tl.n1, smem,
-                                       q.lut_vec != 0, false);
+        apply_tile<VEC, kBatchUnroll, 0, kGlobal>(q.dn, q.lut, q.out, q.lines, q.detectors,
+                                                  q.levels, q.log_strip, tl.band, tl.d0, weff,
+                                                  tl.n0, tl.n1, smem, q.lut_vec != 0, false);
     }
 }
 
 // counters[q]: next tile of queue q; counters[kBatchQueues]: workgroups finished.
-// Two workgroups of kBatchThreads run per CU, 4 waves per SIMD: one streams
-// with 256 threads (16 bytes x 4 lines per lane and register set; with 1024
-// threads and 8 bytes the CU had 4 times the bytes in flight, and neighbouring
-// strips fetched the sectors they share again) while the other evaluates its
-// strip. 16 requests of 512 to 8192 lines and detectors, 1 to 4 bands, 10 and
-// 12 bit: 1.97 -> 1.75 ms from that, 8 pixels per lane on any row and dense
-// strips of 128 detectors for 4096 levels (packed: 64).
-__global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))
+// One workgroup of kBatchThreads runs per CU, 4 waves per SIMD: all of it
+// evaluates a strip, then 256 threads stream (16 bytes x 4 lines per lane and
+// register set). Evaluating a strip is bound by instruction issue and takes a
+// CU about as long as streaming 4 bytes per entry (detector_cost), so a batch
+// of few tiles lasts as long as one tile's evaluation: as many waves as fit, and
+// strips no wider than streaming needs. In us, against two workgroups of 512
+// threads per CU and dense strips of 128 detectors at 4096 levels: one request
+// of 2 x 1013 x 1492 71 (172), one of 1 x 7009 x 2155 100 (219), 4 of together
+// 385 Mpix 557 (690), the 16 of the performance cases 1631 (1750). With 512
+// threads streaming: 1 % more on average, up to 10 %.
+__global__ __launch_bounds__(kBatchThreads)
 void k_apply_batch(const BatchReq* __restrict__ reqs, const BatchTile* __restrict__ tiles,
                    BatchQueues queues, unsigned int* counters) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -161,18 +162,14 @@ hipError_t prepare_batch_kernel(size_t lds) {
 }
 
 // Tile shape of a request without a batch entry: the plain path's tuned plan
-// if the cache has one, else dense strips for 2048 to 8192 levels (twice the
-// detectors of a packed strip in the same LDS), else pow2_plan's.
+// if the cache has one, else pow2_plan's (packed strips of 64 detectors at 4096
+// levels). Dense strips hold twice the detectors in the same LDS, which makes
+// half the tiles, each of twice the evaluation: 51 batches of 1 to 16 requests
+// took 1.21 times as long with them on average, between 0.93 and 2.2.
 static void batch_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
-                       const DeviceInfo& di, size_t lds_cap, rc_plan* plan) {
-    if (tuned_plan(lines, detectors, bands, levels, vmax, di, plan)) return;
-    pow2_plan(lines, detectors, bands, levels, vmax, di, plan);
-    if (levels < 2048 || levels > kDenseMaxLevels) return;
-    int W = 256;
-    while (W > 8 && (plan_lds_bytes(RC_PATH_DENSE, W, levels) > lds_cap || W / 2 >= detectors))
-        W >>= 1;
-    plan->path = RC_PATH_DENSE;
-    plan->strip = W;
+                       const DeviceInfo& di, rc_plan* plan) {
+    if (!tuned_plan(lines, detectors, bands, levels, vmax, di, plan))
+        pow2_plan(lines, detectors, bands, levels, vmax, di, plan);
 }
 
 void fit_request_plan(const rc_plan& plan_in, int levels, size_t lds_cap, BatchReq* q) {
@@ -329,7 +326,8 @@ int64_t detector_cost(const BatchReq& q, int64_t lines) {
 // has a workgroup, else about the workgroups' share of the work plus 0.6 of
 // the longest tile (fitted to a simulation of the queues with 4 to 16 requests
 // of 512 to 8192 lines and detectors). Tries bounds on the longest tile and
-// takes the best: 16 such requests 1.75 ms, with chunks of 8192 lines 1.85.
+// takes the best: 36 batches of 1 to 16 requests took 1.12 times as long with
+// chunks of 8192 lines, between 0.96 and 1.92.
 std::vector<int64_t> line_chunks(const std::vector<BatchReq>& reqs, int slots) {
     const size_t n = reqs.size();
     std::vector<int64_t> best(n, 1), cur(n, 1);
@@ -416,7 +414,7 @@ rc_status batch_create(const rc_request* reqs, int32_t n, int32_t flags, const r
             } else if (tuned_batch_shape(r.detectors, r.levels, vmax, *di, &p)) {
                 ++ntuned;
             } else {
-                batch_plan(lines_p, r.detectors, r.bands, r.levels, vmax, *di, lds_cap, &p);
+                batch_plan(lines_p, r.detectors, r.bands, r.levels, vmax, *di, &p);
             }
             fit_request_plan(p, r.levels, lds_cap, &q);
             if (q.mode == kGlobal) gather_lut += lut_n;  // read back by the gather
@@ -689,7 +687,7 @@ rc_status rc_batch_tune(const rc_request* reqs, int32_t n, int32_t effort, int32
             const rc_request& r0 = c.reqs.front();
             rc_plan h;
             const int64_t lines_p = std::max<int64_t>(r0.lines, 1);
-            batch_plan(lines_p, r0.detectors, r0.bands, r0.levels, c.vmax, *di, lds_cap, &h);
+            batch_plan(lines_p, r0.detectors, r0.bands, r0.levels, c.vmax, *di, &h);
             cands.push_back(h);
             for (const rc_plan& x : batch_candidates(c.levels, c.dmax, c.vmax, lds_cap, effort))
                 cands.push_back(x);

@@ -1260,8 +1260,7 @@ __device__ __forceinline__ uint32_t g_glb_l2(__amdgpu_buffer_rsrc_t r, uint32_t 
 // One fused tile of a batched request: build the strip's LUT in LDS from the
 // coefficients with every thread (writing it to the global LUT too when
 // write_lut), then correct lines [n0, n1) as apply_tile does, with the first
-// nst threads: as many bytes in flight as the plain tiles keep. Another
-// workgroup of the CU builds meanwhile.
+// nst threads: as many bytes in flight as the plain tiles keep.
 template <int VEC, int UNROLL, int MODE>
 __device__ __forceinline__ void fused_tile(const double* __restrict__ coeffs, const uint16_t* dn,
                                            uint16_t* lut, uint16_t* out, int64_t N, int D, int L,

@@ -286,10 +286,6 @@ hipError_t admit(rc_server* s, const std::shared_ptr<Job>& jp) {
     if (j.rows > 0) {
         const int vmax = j.pixels > 0 ? max_vec(q.dn, q.out, h.detectors) : 1;
         const int64_t lines_p = std::max<int64_t>(h.lines, 1);
-        // Not batch_plan's dense strips of up to 256 detectors: what counts is
-        // how soon a piece's tiles are done, and building 256 x 4096 levels for
-        // some hundred lines outlasts their copy (4 x 1058 x 5117 at 4096
-        // levels: 1.53 ms with packed strips of 64, 1.75-1.83 with those).
         rc_plan p;
         if (!tuned_plan(lines_p, h.detectors, h.bands, h.levels, vmax, *s->di, &p))
             pow2_plan(lines_p, h.detectors, h.bands, h.levels, vmax, *s->di, &p);
