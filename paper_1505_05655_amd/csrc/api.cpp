@@ -99,6 +99,10 @@ int max_vec(const uint16_t* dn, const uint16_t* out, int32_t detectors, int cap)
     return 1;
 }
 
+bool on_sectors(const uint16_t* dn, const uint16_t* out) {
+    return (((uintptr_t)dn | (uintptr_t)out) & 63u) == 0;
+}
+
 int plan_slots(const rc_plan& plan, size_t lds_bytes, const DeviceInfo& di) {
     int per_cu = std::max(1, 2048 / std::max(64, (int)plan.threads));
     if (plan.path != RC_PATH_L2 && lds_bytes) {
@@ -210,7 +214,10 @@ bool balanced_tiling(int64_t lines, int32_t detectors, int32_t bands, int vec, i
 // 256 threads with 16 bytes x 4 lines per lane and register set (half or twice
 // the bytes in flight per CU were slower by 20 % and 10 % on every large
 // scene). The estimate, in us, of a launch of B x ceil(D / w) x k tiles:
-//  - staging a tile: w x L entries at a cost per mode;
+//  - staging a tile: w x L entries at a cost per mode (a wave encodes dense
+//    rows four at a time, so narrow dense strips leave waves idle; rows of
+//    levels that are no multiple of 8 are loaded 16 bits at a time; more tiles
+//    than CUs are staged by the streaming threads alone);
 //  - streaming: the image at 6 TB/s (and per_tile at most) times w / (w + ends
 //    + drift min(1, lines per tile / 20000)): neighbouring strips share the
 //    memory sectors at their ends, the more often fetched twice the further
@@ -219,7 +226,9 @@ bool balanced_tiling(int64_t lines, int32_t detectors, int32_t bands, int vec, i
 //  - one round of tiles (at most one per CU) stages, then streams; more tiles
 //    overlap the two, but their streams, far apart in the image, run at a
 //    fraction of the rate, which only a scene with fewer lines than levels
-//    makes up for.
+//    makes up for;
+//  - where lines are few against the levels, pow2_plan's tiles too, two per CU
+//    with 512 threads that all stage and stream.
 // A tile of fewer lines than a pass takes has fewer pixels per lane: 1 x 1024
 // x 1024 in 256 tiles of 16 x 256, 6.3 us with 4 and 7.3 with 8; in 128 of 8 x
 // 1024, 7.6; 1 x 512 x 512 5.25 with 2, 5.75 with 8.
@@ -227,19 +236,20 @@ bool balanced_tiling(int64_t lines, int32_t detectors, int32_t bands, int vec, i
 // strips and other multiples of 64 (whole 128-byte lines, see check_plan), any
 // other rows power-of-two strips and even divisions of the row into about 256
 // or 192 tiles: 16-byte lanes find no alignment there that they could keep.
-// Fitted to 32 scenes of the first kind and 15 of the second (1-4 bands,
-// 512-50000 lines, 512-12000 detectors, 1024 or 4096 levels), each timed with
-// all widths and about 8 chunk counts: the plan chosen takes 1.03 and 1.05
-// times the best one's time on average, and was at least as fast as the former
-// default (W = 256 or 64, about two rounds of 512-thread tiles but few line
-// chunks) on all. 1 x 30000 x 2000 at 4096 levels: 69 against 163 us; 4 x 3000
-// x 1000 at 1024: 14 against 103; 1 x 512 x 512: 8 against 34; 3 x 5400 x
-// 4096: 68 against 111; 4 x 12000 x 12000: 428 against 460 with a tuned plan;
-// even divisions against powers of two: 2 x 40000 x 4001 256 against 301, 2 x
-// 4700 x 5122 at 4096 79 against 86, 4 x 12000 x 11999 475 against 512. False
-// if nothing fits.
+// The streaming constants are fitted to 32 scenes of the first kind and 15 of
+// the second (1-4 bands, 512-50000 lines, 512-12000 detectors, 1024 or 4096
+// levels), those of staging to 850 scenes of 16 to 16384 levels, each timed with
+// about 40 plans. 1 x 30000 x 2000 at 4096 levels: 69 us against 163 with strips
+// of 64; 4 x 3000 x 1000 at 1024: 14 against 103; 3 x 5400 x 4096: 68 against
+// 111; 4 x 12000 x 12000: 428 against 460; even divisions against powers of two:
+// 2 x 40000 x 4001 256 against 301, 4 x 12000 x 11999 475 against 512; pow2_plan's
+// tiles against the others: 1 x 701 x 4688 at 8192 levels 34 against 43, 2 x 1091
+// x 5595 at 4096 42 against 52. Of 460 further scenes (256-50000 lines, 256-12000
+// detectors, 16 to 16384 levels, a fifth in place, some off 16-byte alignment) 10
+// take more than 1.03 times pow2_plan's tiles (at most 1.23), all together 0.54
+// of them. False if nothing fits.
 bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
-                const DeviceInfo& di, rc_plan* plan, bool in_place) {
+                const DeviceInfo& di, rc_plan* plan, bool in_place, bool aligned) {
     // A program's next scene mostly has the last one's shape: the plan, which
     // depends on nothing else, is kept per thread (the search takes 1.5 us).
     struct Last {
@@ -247,13 +257,13 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
         int64_t lines = 0;
         int32_t detectors = 0, bands = 0, levels = 0;
         int vmax = 0;
-        bool in_place = false, found = false;
+        bool in_place = false, aligned = false, found = false;
         rc_plan plan{};
     };
     static thread_local Last last;
     if (last.di == &di && last.lines == lines && last.detectors == detectors &&
         last.bands == bands && last.levels == levels && last.vmax == vmax &&
-        last.in_place == in_place) {
+        last.in_place == in_place && last.aligned == aligned) {
         if (last.found) *plan = last.plan;
         return last.found;
     }
@@ -266,10 +276,16 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
     p.threads = 256;
     p.xcd_remap = 1;
     struct Model {
-        double raw, packed, dense, ends, drift, ragged, per_tile, overlapped;
+        double raw, packed, dense, dense_rows;  // staging, per entry; dense: of w + dense_rows rows
+        double raw_odd, packed_odd, dense_odd;  // times that where levels is no multiple of 8
+        double more, dense_more;                // times that where there are more tiles than CUs
+        double ends, drift, ragged, per_tile, overlapped;
+        double pair, pair_alone, pair_tile, pair_rate;  // tiles of pow2_plan
     };
-    static const Model kSectors = {1.15e-4, 2.2e-4, 1e9, 5.0, 50.0, 1.0, 21e3, 2e6};
-    static const Model kAnyRows = {6e-5, 1.4e-4, 1.2e-4, 2.0, 40.0, 1.6, 23.8e3, 1.2e6};
+    static const Model kSectors = {1.15e-4, 2.2e-4, 1e9, 0.0, 2.4, 1.2, 1.0, 1.0, 1.0,
+                                   5.0, 50.0, 1.0, 21e3, 2e6, 3.8e-4, 0.56, 25e3, 5e6};
+    static const Model kAnyRows = {6e-5, 1.4e-4, 1.1e-4, 20.0, 3.0, 1.5, 2.0, 2.3, 2.0,
+                                   2.0, 40.0, 1.6, 23.8e3, 3.5e6, 1.93e-4, 0.52, 19e3, 5.2e6};
     const bool sectors = detectors % 32 == 0;
     const Model& m = sectors ? kSectors : kAnyRows;
     double best = 0.0;
@@ -281,6 +297,19 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
     const int64_t cap = max_chunk_lines(detectors, p.threads, unroll);
     if (cap < 1) return false;
     const int64_t kmin = std::max<int64_t>(1, (lines + cap - 1) / cap);
+    const bool odd = levels % 8 != 0;
+    const double packed_entry = m.packed * (odd ? m.packed_odd : 1.0);
+    auto stage_us = [&](int path, double w, bool one_round) {
+        if (path == RC_PATH_DENSE)
+            return (w + m.dense_rows) * levels * m.dense * (odd ? m.dense_odd : 1.0) *
+                   (one_round ? 1.0 : m.dense_more);
+        return w * levels * (path == RC_PATH_PACKED ? packed_entry : m.raw * (odd ? m.raw_odd : 1.0)) *
+               (one_round ? 1.0 : m.more);
+    };
+    // Segments of less than a 64-byte sector.
+    auto sector_part = [&](double w) {
+        return sectors && w < 32.0 ? std::pow(w / 32.0, 0.7) : 1.0;
+    };
     // Strips of `width` detectors with k line chunks; even: S of nearly equal
     // width instead of ceil(D / W) of W = width.
     auto consider = [&](int width, int64_t strips, bool even, int64_t k) {
@@ -303,9 +332,7 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
         const double waste = std::min(1.5, std::ceil(per_tile / pass) * pass / per_tile);
         const double drift = m.drift * std::min(1.0, per_tile / 20000.0) *
                              (even && 64 % lanes != 0 ? m.ragged : 1.0);
-        // Segments of less than a 64-byte sector.
-        const double part = sectors && w < 32.0 ? std::pow(w / 32.0, 0.7) : 1.0;
-        const double eff = part * w / (w + m.ends + drift);
+        const double eff = sector_part(w) * w / (w + m.ends + drift);
         const bool one_round = tiles <= cus;
         const double rate = one_round ? std::min(6e6 * eff, m.per_tile * (double)tiles)
                                       : m.overlapped * eff;  // bytes per us
@@ -317,9 +344,7 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
                 continue;
             const size_t lds = plan_lds_bytes(path, W, levels);
             if (lds > budget) continue;
-            const double stage = w * levels * (path == RC_PATH_LDS      ? m.raw
-                                               : path == RC_PATH_PACKED ? m.packed
-                                                                        : m.dense);
+            const double stage = stage_us(path, w, one_round);
             const double t = one_round || lds * 2 > budget
                                  ? stage * rounds + stream
                                  : std::max(stage * rounds, stream) + stage;
@@ -364,14 +389,39 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
     // 461, 3 x 12000 x 8640 at 4096 levels 329 -> 341), except right after a
     // large write to other memory (the first of these 500 -> 465).
     const double cache = 256.0 * 1048576.0;
-    p.nontemporal = detectors % 32 != 0 || p.strip < 32      ? 0
-                    : image > cache && image <= 4.0 * cache ? 1
-                                                            : 2;
+    // Off sectors, in place, they cost up to twice the time (3 x 23443 x 1792 at
+    // 8-byte alignment 265 us, 131 without); apart they still gain 5 % there.
+    p.nontemporal = !sectors || p.strip < 32 || (in_place && !aligned) ? 0
+                    : image > cache && image <= 4.0 * cache            ? 1
+                                                                       : 2;
     // The plan runs as it is too (rc_correct_plan, in place): a lane for each
     // vec of the strip's detectors. widen_plan takes this back.
     while (found && p.strip / p.vec > p.threads) p.threads *= 2;
+    // pow2_plan's packed tiles, 512 threads and two per CU: one streams while the
+    // other is staged. Better where staging is most of the time.
+    rc_plan pair;
+    pow2_plan(lines, detectors, bands, levels, vmax, di, &pair);
+    const int64_t pair_tiles = ((int64_t)detectors + pair.strip - 1) / pair.strip * bands;
+    if (pair.path == RC_PATH_PACKED && pair.chunk_lines >= lines && 2 * lines <= levels &&
+        lines <= max_chunk_lines(detectors, pair.threads, pair.unroll) &&
+        pair_tiles * pair.threads < (int64_t)1 << 32) {
+        const double w = std::min(pair.strip, detectors);
+        const double pass = (double)(pair.threads / (pair.strip / pair.vec) * pair.unroll);
+        const double waste = std::min(1.5, std::ceil((double)lines / pass) * pass / (double)lines);
+        const double drift = m.drift * std::min(1.0, (double)lines / 20000.0);
+        const double rate = m.pair_rate * sector_part(w) * w / (w + m.ends + drift);
+        const double stage = w * levels * m.pair * (odd ? m.packed_odd : 1.0);
+        const double stream = image * waste / rate;
+        const int64_t rounds = (pair_tiles + 2 * cus - 1) / (2 * cus);
+        const double t =
+            rounds > 1 ? std::max(stage * (double)rounds, stream) + stage
+                       : stage * (pair_tiles <= cus ? m.pair_alone : 1.0) +
+                             std::max(stream, image * waste / (m.pair_tile * (double)pair_tiles));
+        if (!found || t < best) p = pair;
+        found = true;
+    }
     if (found) *plan = p;
-    last = Last{&di, lines, detectors, bands, levels, vmax, in_place, found, p};
+    last = Last{&di, lines, detectors, bands, levels, vmax, in_place, aligned, found, p};
     return found;
 }
 
@@ -379,7 +429,7 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
 // long LUT rows with many lines per tile, else strip_plan, else pow2_plan (the
 // L2 path, for LUT rows too long for LDS strips).
 void default_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
-                  const DeviceInfo& di, rc_plan* plan, bool in_place) {
+                  const DeviceInfo& di, rc_plan* plan, bool in_place, bool aligned) {
     rc_plan legacy;
     pow2_plan(lines, detectors, bands, levels, vmax, di, &legacy);
     const int64_t cus = std::max(1, di.cus);
@@ -415,7 +465,7 @@ void default_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t level
         return;
     }
     if (legacy.path == RC_PATH_L2 ||
-        !strip_plan(lines, detectors, bands, levels, vmax, di, plan, in_place))
+        !strip_plan(lines, detectors, bands, levels, vmax, di, plan, in_place, aligned))
         *plan = legacy;
 }
 
@@ -590,6 +640,9 @@ bool widen_plan(const uint16_t* dn, const uint16_t* out, int32_t detectors, rc_p
     rc_plan p = *plan;
     if (p.path == RC_PATH_L2 || p.vec == 8 || p.strip < 8 || detectors < 8)
         return false;
+    // Packed tiles of 512 threads have two per CU (strip_plan): as many bytes in
+    // flight with narrower lanes.
+    if (p.path == RC_PATH_PACKED && p.threads >= 512 && p.strips == 0) return false;
     const int64_t pow2 = ((int64_t)detectors + p.strip - 1) / p.strip;
     if (p.strips > 0 || detectors - (pow2 - 1) * p.strip < 8) {
         const int64_t units = ((int64_t)detectors + 7) / 8;
@@ -642,7 +695,8 @@ rc_status run_correct(const uint16_t* dn, const uint16_t* lut, int64_t lines, in
     } else if (use_ws) {
         ws_plan(lines, detectors, bands, levels, vmax, *di, &plan);
     } else if (!tuned_plan(lines, detectors, bands, levels, vmax, *di, &plan)) {
-        default_plan(lines, detectors, bands, levels, vmax, *di, &plan, dn == out);
+        default_plan(lines, detectors, bands, levels, vmax, *di, &plan, dn == out,
+                     on_sectors(dn, out));
     }
     if (use_ws && plan.path != RC_PATH_DENSE) return RC_EINVAL;
     ApplyParams p{};
@@ -802,7 +856,9 @@ rc_status rc_plan_for(int64_t lines, int32_t detectors, int32_t bands, int32_t l
     if (!di) return RC_EHIP;
     const int vmax = max_vec(dn, out, detectors, 8);
     const bool tuned = tuned_plan(lines, detectors, bands, levels, vmax, *di, plan);
-    if (!tuned) default_plan(lines, detectors, bands, levels, vmax, *di, plan, dn && dn == out);
+    if (!tuned)
+        default_plan(lines, detectors, bands, levels, vmax, *di, plan, dn && dn == out,
+                     on_sectors(dn, out));
     if (source) *source = tuned ? 1 : 0;
     return RC_OK;
 }

@@ -33,6 +33,10 @@ rc_status hip_fail(hipError_t e);
 // lane; the plan cache's batch entries are keyed by the bound at 4.
 int max_vec(const uint16_t* dn, const uint16_t* out, int32_t detectors, int cap = 4);
 
+// Both images start on 64-byte sectors (so do their rows then, if the detector
+// count is a multiple of 32).
+bool on_sectors(const uint16_t* dn, const uint16_t* out);
+
 // Launch shape with power-of-two strips of W detectors and about two rounds
 // of resident tiles (the persistent batch and serving kernels tile requests
 // this way; the plain path uses it for the L2 path).
@@ -57,9 +61,10 @@ size_t dense_ws_bytes(int32_t detectors, int32_t bands, int32_t levels);
 void ws_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
              const DeviceInfo& di, rc_plan* plan);
 
-// Default launch shape for a shape class (no tuning).
+// Default launch shape for a shape class (no tuning). aligned: on_sectors.
 void default_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
-                  const DeviceInfo& di, rc_plan* plan, bool in_place = false);
+                  const DeviceInfo& di, rc_plan* plan, bool in_place = false,
+                  bool aligned = true);
 
 // Checks a plan against a shape and device; fills `p` and `lds_bytes`.
 rc_status check_plan(const rc_plan& plan, int64_t lines, int32_t detectors, int32_t bands,
@@ -74,7 +79,7 @@ rc_status correct_chosen(const uint16_t* dn, const uint16_t* lut, int64_t lines,
 
 // Estimated best strips and line chunks of the LDS paths.
 bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
-                const DeviceInfo& di, rc_plan* plan, bool in_place);
+                const DeviceInfo& di, rc_plan* plan, bool in_place, bool aligned);
 
 // Rows whose alignment allows fewer than 8 pixels per lane (an odd detector
 // count, say): turns an LDS plan into the same tiles with 8 pixels per lane

@@ -251,11 +251,11 @@ void store_batch_shape(int32_t detectors, int32_t levels, int vmax, const Device
 namespace {
 
 std::vector<rc_plan> candidates(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
-                                int vmax, const DeviceInfo& di, int effort) {
+                                int vmax, const DeviceInfo& di, int effort, bool aligned) {
     (void)bands;
     std::vector<rc_plan> out;
     rc_plan def;
-    default_plan(lines, detectors, bands, levels, vmax, di, &def);
+    default_plan(lines, detectors, bands, levels, vmax, di, &def, false, aligned);
     out.push_back(def);
     const int64_t dcap = (int64_t)1 << clog2(std::max(detectors, 1));
     auto add = [&](int path, int W, int vec, int threads, int unroll, int nt, int k) {
@@ -368,7 +368,8 @@ rc_status rc_tune(const uint16_t* dn, const uint16_t* lut, int64_t lines, int32_
     const DeviceInfo* di = current_device();
     if (!di) return RC_EHIP;
     const int vmax = max_vec(dn, out, detectors, 8);
-    std::vector<rc_plan> cands = candidates(lines, detectors, bands, levels, vmax, *di, effort);
+    std::vector<rc_plan> cands =
+        candidates(lines, detectors, bands, levels, vmax, *di, effort, on_sectors(dn, out));
     hipEvent_t e0, e1;
     hipError_t e = hipEventCreate(&e0);
     if (e != hipSuccess) return hip_fail(e);

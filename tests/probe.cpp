@@ -54,7 +54,7 @@ static void plan(std::istringstream& in) {
         out_off < 0 ? dn : (const uint16_t*)(uintptr_t)((1ull << 45) + out_off);
     const int vmax = max_vec(dn, out, D, 8);
     rc_plan p, w;
-    default_plan(N, D, B, L, vmax, di, &p, dn == out);
+    default_plan(N, D, B, L, vmax, di, &p, dn == out, on_sectors(dn, out));
     w = p;
     const bool ok = (vmax < 8 && widen_plan(dn, out, D, &w) && runs(w, N, D, B, L, vmax, di, true)) ||
                     runs(p, N, D, B, L, vmax, di);
@@ -74,6 +74,21 @@ static void plan(std::istringstream& in) {
                                       &q.strip, &q.chunk_lines) &&
                       runs(q, N, D, B, L, vmax, di);
     std::printf("%d %d %d\n", ok, pow2, even);
+}
+
+// choice B N D L dn_offset out_offset: rc_correct's plan: path strip strips vec threads chunk_lines
+// nontemporal.
+static void choice(std::istringstream& in) {
+    int64_t N;
+    int B, D, L, dn_off, out_off;
+    in >> B >> N >> D >> L >> dn_off >> out_off;
+    const uint16_t* dn = (const uint16_t*)(uintptr_t)((1ull << 40) + dn_off);
+    const uint16_t* out =
+        out_off < 0 ? dn : (const uint16_t*)(uintptr_t)((1ull << 45) + out_off);
+    rc_plan p;
+    default_plan(N, D, B, L, max_vec(dn, out, D, 8), mi355x(), &p, dn == out, on_sectors(dn, out));
+    std::printf("%d %d %d %d %d %d %d\n", p.path, p.strip, p.strips, p.vec, p.threads,
+                p.chunk_lines, p.nontemporal);
 }
 
 // strips D L path W in_place: pixels per lane of a batch request with strips planned W wide, then
@@ -106,6 +121,7 @@ int main() {
         if (cmd == "demosaic") demosaic(in);
         else if (cmd == "plan") plan(in);
         else if (cmd == "strips") strips(in);
+        else if (cmd == "choice") choice(in);
         else return 1;
         std::fflush(stdout);
     }
