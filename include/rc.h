@@ -380,7 +380,11 @@ rc_status rc_demosaic_gradient(const uint16_t* raw, int32_t images, int32_t heig
  * fastest in the in-memory plan cache under the shape class
  * (arch, CU count, levels, ceil(log2 detectors), ceil(log2 lines), bands,
  * usable vector width). effort 0 = reduced candidate set, 1 = full sweep.
- * `best` / `best_us` (may be NULL) receive the winner and its mean time in us.
+ * `best` / `best_us` (may be NULL) receive the winner and the mean time in us
+ * of rc_correct with it, which for rows that allow fewer than 8 pixels per lane
+ * may run its tiles with 8 (see rc_plan_for; rc_correct_plan does not).
+ * Candidates that rc_correct would run alike are timed once. An entry timed
+ * that way is not used in place where its tiles cannot be run so.
  * Shapes whose image (4 B per pixel) and LUT take less than 512 MiB, and so
  * would stay cached across back-to-back calls, are timed one call at a time,
  * each after a 512 MiB scratch write that evicts the caches and a copy of the

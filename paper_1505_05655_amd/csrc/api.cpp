@@ -660,6 +660,29 @@ bool widen_plan(const uint16_t* dn, const uint16_t* out, int32_t detectors, rc_p
     return true;
 }
 
+rc_status launched_plan(const uint16_t* dn, const uint16_t* out, int64_t lines, int32_t detectors,
+                        int32_t bands, int32_t levels, const DeviceInfo& di, rc_plan* plan,
+                        ApplyParams* p, size_t* lds_bytes) {
+    const int vmax = max_vec(dn, out, detectors, 8);
+    rc_plan wide = *plan;
+    if (vmax < 8 && widen_plan(dn, out, detectors, &wide) &&
+        check_plan(wide, lines, detectors, bands, levels, vmax, di, p, lds_bytes, true) == RC_OK) {
+        *plan = wide;
+        return RC_OK;
+    }
+    return check_plan(*plan, lines, detectors, bands, levels, vmax, di, p, lds_bytes);
+}
+
+bool tuned_plan_for(const uint16_t* dn, const uint16_t* out, int64_t lines, int32_t detectors,
+                    int32_t bands, int32_t levels, const DeviceInfo& di, rc_plan* plan) {
+    const int vmax = max_vec(dn, out, detectors, 8);
+    if (!tuned_plan(lines, detectors, bands, levels, vmax, di, plan)) return false;
+    if (vmax >= 8 || !dn || dn != out) return true;
+    rc_plan apart = *plan, in_place = *plan;
+    return !widen_plan(dn, nullptr, detectors, &apart) ||
+           widen_plan(dn, out, detectors, &in_place);
+}
+
 namespace {
 
 rc_status run_correct(const uint16_t* dn, const uint16_t* lut, int64_t lines, int32_t detectors,
@@ -694,7 +717,7 @@ rc_status run_correct(const uint16_t* dn, const uint16_t* lut, int64_t lines, in
         plan = *forced;
     } else if (use_ws) {
         ws_plan(lines, detectors, bands, levels, vmax, *di, &plan);
-    } else if (!tuned_plan(lines, detectors, bands, levels, vmax, *di, &plan)) {
+    } else if (!tuned_plan_for(dn, out, lines, detectors, bands, levels, *di, &plan)) {
         default_plan(lines, detectors, bands, levels, vmax, *di, &plan, dn == out,
                      on_sectors(dn, out));
     }
@@ -703,13 +726,9 @@ rc_status run_correct(const uint16_t* dn, const uint16_t* lut, int64_t lines, in
     size_t lds_bytes = 0;
     // A plan the caller asked for runs as it is; one the library chose takes 8
     // pixels per lane where that fits.
-    rc_plan wide = plan;
-    if ((!forced || may_widen) && vmax < 8 && widen_plan(dn, out, detectors, &wide) &&
-        check_plan(wide, lines, detectors, bands, levels, vmax, *di, &p, &lds_bytes, true) ==
-            RC_OK)
-        plan = wide;
-    else
-        st = check_plan(plan, lines, detectors, bands, levels, vmax, *di, &p, &lds_bytes);
+    st = forced && !may_widen
+             ? check_plan(plan, lines, detectors, bands, levels, vmax, *di, &p, &lds_bytes)
+             : launched_plan(dn, out, lines, detectors, bands, levels, *di, &plan, &p, &lds_bytes);
     if (st != RC_OK) return st;
     p.dn = dn;
     p.lut = lut;
@@ -855,7 +874,7 @@ rc_status rc_plan_for(int64_t lines, int32_t detectors, int32_t bands, int32_t l
     const DeviceInfo* di = current_device();
     if (!di) return RC_EHIP;
     const int vmax = max_vec(dn, out, detectors, 8);
-    const bool tuned = tuned_plan(lines, detectors, bands, levels, vmax, *di, plan);
+    const bool tuned = tuned_plan_for(dn, out, lines, detectors, bands, levels, *di, plan);
     if (!tuned)
         default_plan(lines, detectors, bands, levels, vmax, *di, plan, dn && dn == out,
                      on_sectors(dn, out));

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <string>
+#include <vector>
 
 #include "kernels.h"
 #include "rc.h"
@@ -89,6 +90,13 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
 // which repeats pixels of the one before it, may be in another wave.
 bool widen_plan(const uint16_t* dn, const uint16_t* out, int32_t detectors, rc_plan* plan);
 
+// Turns a plan the library chose into the one rc_correct launches for these
+// images: widened (widen_plan) where that can run, else as it is. RC_EINVAL if
+// that cannot run either.
+rc_status launched_plan(const uint16_t* dn, const uint16_t* out, int64_t lines, int32_t detectors,
+                        int32_t bands, int32_t levels, const DeviceInfo& di, rc_plan* plan,
+                        ApplyParams* p, size_t* lds_bytes);
+
 // Longest line chunk a tile may have (32-bit buffer offsets); < 1 if none fits.
 int64_t max_chunk_lines(int32_t detectors, int32_t threads, int32_t unroll);
 
@@ -101,6 +109,18 @@ int plan_slots(const rc_plan& plan, size_t lds_bytes, const DeviceInfo& di);
 // Tuned plan from the plan cache, if one matches the shape class.
 bool tuned_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels, int vmax,
                 const DeviceInfo& di, rc_plan* plan);
+
+// The same for these images (dn may be NULL): false also in place, where the
+// plan was timed widened (rc_tune) and in place it cannot be.
+bool tuned_plan_for(const uint16_t* dn, const uint16_t* out, int64_t lines, int32_t detectors,
+                    int32_t bands, int32_t levels, const DeviceInfo& di, rc_plan* plan);
+
+// The plans rc_tune times for these images, the default first: no two that
+// rc_correct would launch alike (rows that allow fewer than 8 pixels per lane
+// run most candidates widened), of such the first.
+std::vector<rc_plan> tune_candidates(const uint16_t* dn, const uint16_t* out, int64_t lines,
+                                     int32_t detectors, int32_t bands, int32_t levels,
+                                     const DeviceInfo& di, int effort);
 
 // Batch entries of the plan cache: the persistent batch kernel's tile shape
 // (path, strip, vec of *plan) for requests of a class (levels,

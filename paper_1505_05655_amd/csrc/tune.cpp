@@ -353,6 +353,29 @@ std::vector<rc_plan> candidates(int64_t lines, int32_t detectors, int32_t bands,
 }
 
 }  // namespace
+
+std::vector<rc_plan> tune_candidates(const uint16_t* dn, const uint16_t* out, int64_t lines,
+                                     int32_t detectors, int32_t bands, int32_t levels,
+                                     const DeviceInfo& di, int effort) {
+    const int vmax = max_vec(dn, out, detectors, 8);
+    const std::vector<rc_plan> all =
+        candidates(lines, detectors, bands, levels, vmax, di, effort, on_sectors(dn, out));
+    std::vector<rc_plan> kept, launched;
+    for (const rc_plan& c : all) {
+        rc_plan run = c;
+        ApplyParams p{};
+        size_t lds = 0;
+        if (launched_plan(dn, out, lines, detectors, bands, levels, di, &run, &p, &lds) != RC_OK)
+            continue;
+        auto alike = [&](const rc_plan& x) { return std::memcmp(&x, &run, sizeof run) == 0; };
+        if (std::any_of(launched.begin(), launched.end(), alike)) continue;
+        kept.push_back(c);
+        launched.push_back(run);
+    }
+    if (kept.empty()) kept.push_back(all.front());  // none can run: the default
+    return kept;
+}
+
 }  // namespace rc
 
 using namespace rc;
@@ -368,8 +391,8 @@ rc_status rc_tune(const uint16_t* dn, const uint16_t* lut, int64_t lines, int32_
     const DeviceInfo* di = current_device();
     if (!di) return RC_EHIP;
     const int vmax = max_vec(dn, out, detectors, 8);
-    std::vector<rc_plan> cands =
-        candidates(lines, detectors, bands, levels, vmax, *di, effort, on_sectors(dn, out));
+    const std::vector<rc_plan> cands =
+        tune_candidates(dn, out, lines, detectors, bands, levels, *di, effort);
     hipEvent_t e0, e1;
     hipError_t e = hipEventCreate(&e0);
     if (e != hipSuccess) return hip_fail(e);

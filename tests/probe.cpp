@@ -113,6 +113,38 @@ static void strips(std::istringstream& in) {
     std::printf("\n");
 }
 
+// tune B N D L dn_offset: number of rc_tune's candidates, and of different plans they run.
+static void tune(std::istringstream& in) {
+    int64_t N;
+    int B, D, L, dn_off;
+    in >> B >> N >> D >> L >> dn_off;
+    const DeviceInfo di = mi355x();
+    const uint16_t* dn = (const uint16_t*)(uintptr_t)((1ull << 40) + dn_off);
+    const uint16_t* out = (const uint16_t*)(uintptr_t)(1ull << 45);
+    std::vector<std::string> runs;
+    const std::vector<rc_plan> cands = tune_candidates(dn, out, N, D, B, L, di, 1);
+    for (rc_plan p : cands) {
+        ApplyParams a{};
+        size_t lds = 0;
+        if (launched_plan(dn, out, N, D, B, L, di, &p, &a, &lds) == RC_OK)
+            runs.push_back(std::string((const char*)&p, sizeof p));
+    }
+    std::sort(runs.begin(), runs.end());
+    const size_t distinct = std::unique(runs.begin(), runs.end()) - runs.begin();
+    std::printf("%zu %zu\n", cands.size(), distinct);
+}
+
+// tuned B N D L dn_offset in_place: whether an entry of the plan cache serves the images.
+static void tuned(std::istringstream& in) {
+    int64_t N;
+    int B, D, L, dn_off, in_place;
+    in >> B >> N >> D >> L >> dn_off >> in_place;
+    const uint16_t* dn = (const uint16_t*)(uintptr_t)((1ull << 40) + dn_off);
+    const uint16_t* out = in_place ? dn : (const uint16_t*)(uintptr_t)((1ull << 45) + dn_off);
+    rc_plan p;
+    std::printf("%d\n", tuned_plan_for(dn, out, N, D, B, L, mi355x(), &p));
+}
+
 int main() {
     std::string line, cmd;
     while (std::getline(std::cin, line)) {
@@ -122,6 +154,8 @@ int main() {
         else if (cmd == "plan") plan(in);
         else if (cmd == "strips") strips(in);
         else if (cmd == "choice") choice(in);
+        else if (cmd == "tune") tune(in);
+        else if (cmd == "tuned") tuned(in);
         else return 1;
         std::fflush(stdout);
     }

@@ -22,10 +22,11 @@ def _binary():
     return out
 
 
-def ask(commands, timeout=60):
-    """The output line of each command."""
+def ask(commands, timeout=60, plan_cache=None):
+    """The output line of each command; plan_cache: the plan cache file (none if not given)."""
+    env = dict(os.environ, RC_TUNE_CACHE=str(plan_cache or "/nonexistent"))
     res = subprocess.run([_binary()], input="\n".join(commands) + "\n", capture_output=True,
-                         text=True, timeout=timeout)
+                         text=True, timeout=timeout, env=env)
     assert res.returncode == 0, f"probe ended with {res.returncode}: {res.stderr}"
     lines = res.stdout.splitlines()
     assert len(lines) == len(commands)
