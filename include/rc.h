@@ -437,12 +437,12 @@ typedef struct {
     int64_t pixels;
     int64_t lut_entries;
     int32_t tuned;        /* requests whose tile shape came from a batch entry of the plan
-                             cache (rc_batch_tune); the others use the plain path's plan */
+                             cache (rc_batch_tune); the others take that of a plain tuned plan,
+                             or power-of-two strips for the batch's LDS */
     int32_t fused;        /* requests whose LUT is written once and never read back: their
-                             tiles evaluate the strip in LDS, or a build kernel writes the
-                             LUT and its dense encoding, which the tiles stage */
-    int64_t lut_gather_entries; /* LUT entries of the other requests (level counts above
-                             8192): written by the build kernel, read back by the gather */
+                             tiles evaluate the strip in LDS */
+    int64_t lut_gather_entries; /* LUT entries of the other requests (levels too many for LDS
+                             strips): written by the build kernel, read back by the gather */
 } rc_batch_stats;
 
 #define RC_BATCH_NO_GRAPH 1 /* flag: launch the two kernels directly on every run */
@@ -452,9 +452,10 @@ typedef struct {
  * (RC_EINVAL as for the plain calls, and also if a buffer written by a
  * request overlaps any other buffer of any request, except a request's out
  * equal to its own dn), picks each request's tile shape (its batch entry of
- * the plan cache, written by rc_batch_tune; else the plain path's plan for
- * the request fitted to the batch kernel), builds the tile queue (longest
- * tiles first), allocates the batch's small device tables and captures the
+ * the plan cache, written by rc_batch_tune; else a plain tuned plan's; else
+ * power-of-two strips), fitted to the batch kernel, which takes 8 pixels per
+ * lane whatever the plan says (1 for rows of fewer than 8 detectors), builds
+ * the tile queue (longest tiles first), allocates the batch's small device tables and captures the
  * LUT build kernel plus the persistent correction kernel into a hipGraph.
  * Synchronises; not capturable. The request buffers must stay valid until
  * rc_batch_destroy; their contents may change between runs.
@@ -469,14 +470,13 @@ rc_status rc_batch_create(const rc_request* reqs, int32_t n, int32_t flags, rc_b
  * Autotunes the batch kernel's tile shape for the shape classes of `reqs`:
  * requests with pixels are grouped by (levels, ceil(log2 detectors), largest
  * usable vector width); for each class, candidate shapes (LDS mode, strip
- * width, pixels per lane) run the class's requests as one batch, launched
+ * width) run the class's requests as one batch, launched
  * directly on `stream` (one warm-up run, then 3 timed with HIP events). The
  * shape rc_batch_create would take without an entry runs first and is kept
  * unless a candidate is at least 2 % faster; the result goes into the plan
  * cache as that class's batch entry (rc_tune_save persists it). effort 0
- * tries the two widest strips and two
- * vector widths per LDS mode; effort 1 one more of each. The runs write the
- * requests' lut and out exactly as rc_batch_run would. Validates as
+ * tries the two widest strips per LDS mode, effort 1 one more. The runs write
+ * the requests' lut and out exactly as rc_batch_run would. Validates as
  * rc_batch_create; synchronises; allocates (each candidate's tables).
  * *classes (if not NULL) = classes tuned.
  * Errors: RC_EINVAL, RC_ENOMEM, RC_EHIP.

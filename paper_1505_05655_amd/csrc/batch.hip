@@ -587,22 +587,20 @@ rc_status batch_create(const rc_request* reqs, int32_t n, int32_t flags, const r
 }
 
 // Candidate tile shapes of the batch kernel for requests with `levels`
-// levels, at most `dmax` detectors and vector width up to vmax: the LDS
-// paths at the widest strip that fits the batch's tile budget and narrower
-// ones, the L2 path at two widths.
-std::vector<rc_plan> batch_candidates(int32_t levels, int32_t dmax, int vmax, size_t lds_cap,
-                                      int effort) {
+// levels and at most `dmax` detectors: the LDS paths at the widest strip that
+// fits the batch's tile budget and narrower ones, the L2 path at two widths
+// (pixels per lane follow from the rows, fit_request_plan).
+std::vector<rc_plan> batch_candidates(int32_t levels, int32_t dmax, size_t lds_cap, int effort) {
     std::vector<rc_plan> out;
     int wcap = 8;
     while (wcap < dmax && wcap < 1024) wcap <<= 1;
     auto add = [&](int path, int W) {
-        const int vec = std::min(vmax, 4);
-        if (W < vec || W > wcap) return;
+        if (W < 1 || W > wcap) return;
         rc_plan p;
         std::memset(&p, 0, sizeof p);
         p.path = path;
         p.strip = W;
-        p.vec = vec;
+        p.vec = 1;
         p.threads = kBatchThreads;
         p.unroll = kBatchUnroll;
         p.chunk_lines = 1;
@@ -689,7 +687,7 @@ rc_status rc_batch_tune(const rc_request* reqs, int32_t n, int32_t effort, int32
             const int64_t lines_p = std::max<int64_t>(r0.lines, 1);
             batch_plan(lines_p, r0.detectors, r0.bands, r0.levels, c.vmax, *di, &h);
             cands.push_back(h);
-            for (const rc_plan& x : batch_candidates(c.levels, c.dmax, c.vmax, lds_cap, effort))
+            for (const rc_plan& x : batch_candidates(c.levels, c.dmax, lds_cap, effort))
                 cands.push_back(x);
         }
         for (const rc_plan& cand : cands) {
