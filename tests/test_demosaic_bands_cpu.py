@@ -19,3 +19,11 @@ def test_band_ends_for_any_number_of_images(method, rows, sectors):
         assert band >= 2 and band % 2 == 0, (images, H, W, band)
         assert band < 2 * max(H, 32), (images, H, W, band)
         assert waves < 1 << 25 or band >= H, (images, H, W, band)
+
+
+def test_gradient_band_heights():
+    pytest.importorskip("torch")
+    from test_gpu_large_images import GRADIENT
+    got = ask(["demosaic gradient %d %d %d 1" % s for s, _ in GRADIENT])
+    assert [int(x) for x in got] == [band for _, band in GRADIENT]
+    assert all(s[1] % band for s, band in GRADIENT)
