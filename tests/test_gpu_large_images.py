@@ -44,7 +44,7 @@ def test_very_wide_rows(shape):
 # test_demosaic_bands_cpu.py), the last band shorter.
 GRADIENT = [((1, 1704, 1056), 10), ((2, 2134, 1056), 12), ((5, 500, 1056), 14), ((4, 1534, 1056), 16),
             ((5, 2134, 1056), 18), ((6, 1274, 1056), 20), ((6, 1532, 2048), 24),
-            ((9, 1876, 1056), 28), ((9, 1790, 2048), 32), ((9, 2046, 2048), 10)]
+            ((9, 1016, 2080), 28), ((9, 1790, 2048), 32), ((9, 2046, 2048), 10)]
 
 
 @pytest.mark.parametrize("shape", [s for s, _ in GRADIENT], ids=str)
