@@ -303,7 +303,8 @@ bool strip_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t levels,
         if (path == RC_PATH_DENSE)
             return (w + m.dense_rows) * levels * m.dense * (odd ? m.dense_odd : 1.0) *
                    (one_round ? 1.0 : m.dense_more);
-        return w * levels * (path == RC_PATH_PACKED ? packed_entry : m.raw * (odd ? m.raw_odd : 1.0)) *
+        const double raw_entry = m.raw * (odd ? m.raw_odd : 1.0);
+        return w * levels * (path == RC_PATH_PACKED ? packed_entry : raw_entry) *
                (one_round ? 1.0 : m.more);
     };
     // Segments of less than a 64-byte sector.
@@ -640,9 +641,12 @@ bool widen_plan(const uint16_t* dn, const uint16_t* out, int32_t detectors, rc_p
     rc_plan p = *plan;
     if (p.path == RC_PATH_L2 || p.vec == 8 || p.strip < 8 || detectors < 8)
         return false;
-    // Packed tiles of 512 threads have two per CU (strip_plan): as many bytes in
-    // flight with narrower lanes.
-    if (p.path == RC_PATH_PACKED && p.threads >= 512 && p.strips == 0) return false;
+    // Packed tiles of 512 threads have two per CU (strip_plan's pair): as many
+    // bytes in flight with narrower lanes. (Not those with as many threads only
+    // because the strip has as many narrow lanes.)
+    if (p.path == RC_PATH_PACKED && p.threads >= 512 && p.strips == 0 &&
+        p.strip / p.vec < p.threads)
+        return false;
     const int64_t pow2 = ((int64_t)detectors + p.strip - 1) / p.strip;
     if (p.strips > 0 || detectors - (pow2 - 1) * p.strip < 8) {
         const int64_t units = ((int64_t)detectors + 7) / 8;

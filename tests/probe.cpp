@@ -91,6 +91,23 @@ static void choice(std::istringstream& in) {
                 p.chunk_lines, p.nontemporal);
 }
 
+// launch B N D L dn_offset out_offset: pixels per lane that rc_correct launches with.
+static void launch(std::istringstream& in) {
+    int64_t N;
+    int B, D, L, dn_off, out_off;
+    in >> B >> N >> D >> L >> dn_off >> out_off;
+    const DeviceInfo di = mi355x();
+    const uint16_t* dn = (const uint16_t*)(uintptr_t)((1ull << 40) + dn_off);
+    const uint16_t* out =
+        out_off < 0 ? dn : (const uint16_t*)(uintptr_t)((1ull << 45) + out_off);
+    rc_plan p;
+    ApplyParams a{};
+    size_t lds = 0;
+    default_plan(N, D, B, L, max_vec(dn, out, D, 8), di, &p, dn == out, on_sectors(dn, out));
+    const bool ok = launched_plan(dn, out, N, D, B, L, di, &p, &a, &lds) == RC_OK;
+    std::printf("%d\n", ok ? p.vec : 0);
+}
+
 // strips D L path W in_place: pixels per lane of a batch request with strips planned W wide, then
 // first detector and width of each strip.
 static void strips(std::istringstream& in) {
@@ -154,6 +171,7 @@ int main() {
         else if (cmd == "plan") plan(in);
         else if (cmd == "strips") strips(in);
         else if (cmd == "choice") choice(in);
+        else if (cmd == "launch") launch(in);
         else if (cmd == "tune") tune(in);
         else if (cmd == "tuned") tuned(in);
         else return 1;

@@ -28,3 +28,10 @@ def test_rows_loaded_16_bits_at_a_time_take_no_raw_strips_of_many_tiles():
 def test_stores_in_place_off_sectors_are_cached(dn, in_place, nontemporal):
     p = choice(1, 5000, 2048, 1024, dn, -1 if in_place else 0)
     assert p["strip"] >= 32 and p["nontemporal"] == nontemporal, p
+
+
+@pytest.mark.parametrize("shape,vec", [((4, 12000, 6001, 1024), 8), ((2, 20000, 2001, 512), 8),
+                                       ((4, 470, 6807, 4096), 1)])
+@pytest.mark.parametrize("out", [0, -1])
+def test_odd_rows_run_wide_but_not_two_tiles_per_cu(shape, vec, out):
+    assert ask(["launch %d %d %d %d 0 %d" % (*shape, out)]) == [str(vec)]
