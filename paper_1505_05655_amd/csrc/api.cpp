@@ -445,7 +445,7 @@ void default_plan(int64_t lines, int32_t detectors, int32_t bands, int32_t level
     const int64_t dstrips = (detectors + wdense - 1) / std::max(wdense, 1);
     const int64_t dtiles = std::max<int64_t>(1, cus / std::max<int64_t>(1, bands * dstrips));
     if (levels >= 2048 && levels <= kDenseMaxLevels && wdense >= 64 && detectors >= 64 &&
-        lines / dtiles >= 4 * (int64_t)levels) {
+        lines / dtiles >= 4 * (int64_t)levels && max_chunk_lines(detectors, 512, 8) >= 1) {
         rc_plan p;
         std::memset(&p, 0, sizeof(p));
         p.path = RC_PATH_DENSE;

@@ -43,7 +43,7 @@ static bool runs(const rc_plan& p, int64_t N, int D, int B, int L, int vmax, con
 
 // plan B N D L dn_offset out_offset (bytes; -1: in place): whether the plan rc_correct takes for
 // the shape can run; whether power-of-two strips (pow2_plan) or, where those are LDS strips, one
-// equal tile per CU (balanced_tiling) can.
+// equal tile per CU (balanced_tiling) can; whether the plan can run as it is.
 static void plan(std::istringstream& in) {
     int64_t N;
     int B, D, L, dn_off, out_off;
@@ -73,7 +73,7 @@ static void plan(std::istringstream& in) {
                       balanced_tiling(N, D, B, q.vec, wmax, di.cus, q.threads, q.unroll, &q.strips,
                                       &q.strip, &q.chunk_lines) &&
                       runs(q, N, D, B, L, vmax, di);
-    std::printf("%d %d %d\n", ok, pow2, even);
+    std::printf("%d %d %d %d\n", ok, pow2, even, runs(p, N, D, B, L, vmax, di));
 }
 
 // choice B N D L dn_offset out_offset: rc_correct's plan: path strip strips vec threads chunk_lines
